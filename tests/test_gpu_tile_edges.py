@@ -1,0 +1,82 @@
+"""GPU parity at the edges of the kernels' tiles: states of one row, of a few lanes of
+a wave, of a wave or a workgroup and one row more, against the oracle at the stated
+bar, with guard words around every buffer that the kernels write."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_39185_amd import workloads as wl
+
+from ._parity import DEV, Bar, say, y_magnitude
+from .test_gpu_checkpoint import _codes_of
+
+pytestmark = pytest.mark.gpu
+GUARD = 64  # elements kept before and after (a multiple of every alignment asked)
+
+
+@pytest.fixture(scope="module")
+def ssmq():
+    import paper_2609_39185_amd as m
+    m.library()
+    return m
+
+
+class Guarded:
+    """A device copy of a host tensor between guard elements that must not change."""
+
+    def __init__(self, t):
+        flat = torch.full((t.numel() + 2 * GUARD,), 77, dtype=t.dtype)
+        flat[GUARD:GUARD + t.numel()] = t.reshape(-1)
+        self.buf = flat.to(DEV)
+        self.t = self.buf[GUARD:GUARD + t.numel()].view(t.shape)
+
+    def check(self, what):
+        b = self.buf.cpu()
+        assert (b[:GUARD] == 77).all() and (b[-GUARD:] == 77).all(), (what, "a guard word changed")
+        return self.t.cpu()
+
+
+# rows (batch, heads) of Mamba-1's 16 entries: one lane, a part of a wave, a wave and
+# one row more, a workgroup of 256 lanes and one row more, a last block with dead waves
+ROWS = [(1, 1), (1, 37), (1, 65), (1, 257), (3, 107)]
+
+
+@pytest.mark.parametrize("b,h", ROWS)
+@pytest.mark.parametrize("fmt,group,rule", [("fp16", 0, "weyl"), ("e4m3", 16, "sr"),
+                                            ("int8", 16, "weyl"), ("int4", 16, "rtn")])
+def test_checkpoint_rows(ssmq, fmt, group, rule, b, h):
+    _checkpoint(ssmq, fmt, group, rule, "mamba1", (b, h, 1, 16, 1))
+
+
+@pytest.mark.parametrize("fmt,group,shape", [
+    ("bf16", 0, (1, 1, 1, 512, 1)), ("bf16", 0, (1, 5, 3, 64, 1)), ("int8", 1024, (1, 3, 1, 1024, 1)),
+    ("e4m3", 128, (1, 3, 3, 128, 1))])
+def test_checkpoint_head_rows(ssmq, fmt, group, shape):
+    _checkpoint(ssmq, fmt, group, "weyl", "mamba2", shape)
+
+
+def _checkpoint(ssmq, fmt, group, rule, family, shape):
+    b, h, p, n, g = shape
+    say(f"case checkpoint {family} {fmt} g{group} {rule} {shape}")
+    A, D = wl.layer_params(family, h, n, 190)
+    x, dt, B, C = wl.step_inputs(b, h, p, n, g, 191)
+    h0 = (np.random.default_rng(192).standard_normal((b, h, p, n)) * 0.3).astype(np.float32)
+    st, y = Guarded(torch.from_numpy(h0)), Guarded(torch.zeros(b, h, p))
+    sc = Guarded(torch.zeros(h0.size // group)) if group else None
+    ssmq.state_update(st.t, sc.t if sc else None, x.to(DEV), dt.to(DEV), A.to(DEV), B.to(DEV),
+                      C.to(DEV), D.to(DEV), y.t, rule=rule, fmt=fmt, scale_group=group, step=5,
+                      layer=1, fp32_state=True)
+    torch.cuda.synchronize()
+    want, wsc, wy = oracle.state_update_fp32_grid(fmt, rule, h0, x.numpy(), dt.numpy(), A.numpy(),
+                                                  B.numpy(), C.numpy(), D.numpy(), step=5, layer=1,
+                                                  block=16, group=group)
+    got, gsc = st.check("state").numpy(), sc.check("scale").numpy() if sc else None
+    bar = Bar(fmt, f"checkpoint edges {fmt} {rule}")
+    if sc:
+        bar.scales(gsc, wsc)
+    bar.codes(_codes_of(fmt, got, gsc, group), _codes_of(fmt, want, wsc, group))
+    _, _, _, h_new = oracle.state_update("fp32", "rtn", h0.view(np.uint32), None, x.numpy(),
+                                         dt.numpy(), A.numpy(), B.numpy(), C.numpy(), D.numpy())
+    bar.y(y.check("y").numpy(), wy, y_magnitude(C.numpy(), h_new, D.numpy(), x.numpy(), h // g))
+    bar.check()
