@@ -250,6 +250,18 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
       return fail(SSMQ_EUNSUPPORTED, "state too large for one launch");
     cfg = ssmq::kRowKernel;
     a.lanes_per_group = scaled ? static_cast<int32_t>(group / 16) : 1;
+    if (d.a_per_state && d.headdim == 1 && d.dstate == ssmq::kChannelN && d.ngroups == 1 && !fp32_state) {
+      const int64_t tiles = (static_cast<int64_t>(d.nheads) * a.lanes_per_row + 255) / 256;
+      // As many sequences per workgroup as leave 2048 workgroups, two rounds of the 1024
+      // that fit the chip (INT8, 5120 channels, batch 225: 1, 2, 3, 5 and 7 sequences
+      // 24.2, 22.3, 21.9, 23.9 and 26.2 us).
+      int64_t per = tiles * d.batch / 2048;
+      per = per < 1 ? 1 : per > ssmq::kChannelBatch ? ssmq::kChannelBatch : per;
+      if ((d.batch + per - 1) / per <= 65535) {
+        cfg = ssmq::kChannelKernel;
+        a.batch_per_wg = static_cast<int32_t>(per);
+      }
+    }
     a.div_headdim = ssmq::make_fastdiv(static_cast<uint32_t>(d.headdim));
   }
   hipError_t e = ssmq::launch_update(a, q->format, q->rule, cfg, d.a_per_state != 0,

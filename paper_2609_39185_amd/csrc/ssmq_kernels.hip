@@ -7,8 +7,12 @@
 //                  threshold -> round -> store, in registers, so the state
 //                  crosses HBM once each way (Section 2 eq. (rec) and eq.
 //                  (dither); Appendix B "Runners", "Formats", "Dithers").
-//   k_update_rows  the same step for any row layout (Mamba-1 with A per (channel,
-//                  n), and Mamba-2 heads smaller than a slab).
+//   k_update_channels  the same step for Mamba-1 layers (heads of one row of 16
+//                  entries, A per (channel, n)): a workgroup takes a tile of channels through
+//                  several sequences.
+//   k_update_rows  the same step for any other row layout (Mamba-2 heads smaller
+//                  than a slab, A per (head, n) with other rows or several B/C groups), and the
+//                  checkpoint write on an fp32 state.
 //   k_requant      fp32 -> codes for fp16 / bf16 / fp32, one chunk per thread.
 //   k_requant_scaled fp32 -> E4M3 / INT8 / INT4 codes with group scales.
 //   k_dither_fill  the 24-bit thresholds themselves.
@@ -36,14 +40,16 @@ __device__ inline void load_floats(const float* p, float (&out)[V]) {
   }
 }
 
-__device__ inline float decay(float dtv, float a) {
-  return static_cast<float>(exp(static_cast<double>(dtv * a)));  // correctly rounded fl32(exp)
-}
+// dA = fl32(exp(fl32(dt A))), correctly rounded.
+__device__ inline float decay(float dtv, float a) { return exp_value(dtv * a); }
 
 // The step size the update uses: dt, plus dt_bias[head] when given, through
 // softplus(v) = log(1 + e^v) (double, one rounding; v itself above 20) when asked.
-__device__ inline float step_size(const UpdateArgs& a, float dtv, int head) {
-  if (a.dt_bias) dtv = dtv + a.dt_bias[head];
+__device__ inline float step_bias(const UpdateArgs& a, int head) {
+  return a.dt_bias ? a.dt_bias[head] : 0.0f;
+}
+__device__ inline float step_size(const UpdateArgs& a, float dtv, float bias) {
+  if (a.dt_bias) dtv = dtv + bias;
   if (a.dt_softplus && !(dtv > 20.0f)) dtv = static_cast<float>(log1p(exp(static_cast<double>(dtv))));
   return dtv;
 }
@@ -123,7 +129,7 @@ void k_update_slab(UpdateArgs a) {
   const float Dv = a.D ? a.D[hh] : 0.0f;
 
   if (t < 64) {
-    const float dte = step_size(a, dt_in, hh);
+    const float dte = step_size(a, dt_in, step_bias(a, hh));
     const float d = decay(dte, a.A[hh]);
     if (t == 0) { sh[0] = d; sh[2] = dte; sDone = 0; }
   }
@@ -435,7 +441,7 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
     decode_chunk<F>(load_stream<chunk_t<F>>(state + chunk_bytes_at<F>(e)), hp);
   }
   const float xv = a.x[row];
-  const float dtv = step_size(a, a.dt[bh], hh);
+  const float dtv = step_size(a, a.dt[bh], step_bias(a, hh));
   const float Dv = a.D ? a.D[hh] : 0.0f;
   float Bv[V], Cv[V], dA[V];
   load_floats<V>(a.B + (static_cast<int64_t>(b) * a.ngroups + g) * a.dstate + n0, Bv);
@@ -486,6 +492,129 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
       if constexpr (Traits<F>::scaled) v[k] = v[k] * s;
     span.store(v);
   } else {
+    if (live) store_stream(state + chunk_bytes_at<F>(e), out);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Mamba-1 layers: heads of one row of 16 entries (headdim 1, dstate 16), A per
+// (channel, n), B and C shared by all channels of a sequence.
+// ---------------------------------------------------------------------------
+// A workgroup takes a tile of channels (256 chunks, one per lane) through
+// batch_per_wg sequences. Vector issue bounds the step: of about 28 instructions per
+// INT8 entry 15 are its own exp(dt A), so that takes the short table form. A and D
+// stay in registers, B and C of the workgroup's sequences are staged in LDS, and the
+// next sequence's state and x load while the current one is computed (one chunk per
+// lane and launch reads A anew for every sequence, 4 bytes per entry against 2 of INT8
+// state, and waits for three rounds of loads one after another). 5120 channels, batch
+// 225, INT8 blocks of 16, Weyl: 26.1 -> 22.2 us against the row kernel.
+// Four waves per SIMD: at the 128 registers of that bound nothing spills.
+template <int F, int R>
+__global__ __launch_bounds__(256, 4) void k_update_channels(UpdateArgs a) {
+  constexpr int V = Traits<F>::V;
+  const int t = threadIdx.x;
+  constexpr int N = kChannelN, LR = N / V;  // lanes per row: 1, 2 or 4; a scaled row is one group
+  const int cc = t & (LR - 1);
+  const int n0 = cc * V;
+  const int tile = static_cast<int>(blockIdx.x) * (256 / LR) + t / LR;
+  const bool live = tile < a.nheads;  // whole rows (and groups) are live or dead together
+  const int ch = live ? tile : 0;
+  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * a.batch_per_wg;
+  const int nb = static_cast<int>(min(static_cast<int64_t>(a.batch_per_wg), a.batch - b0));
+
+  __shared__ float4 sBC[kChannelBatch * 2 * N / 4];  // per sequence: B, then C
+  __shared__ double sExp[kExpTable];
+  stage_exp_table(sExp, t, 256);
+  constexpr int NQ = N / 4;
+  static_assert(kChannelBatch * 2 * NQ <= 256, "one float4 of B or C per thread");
+  const bool has_bc = t < nb * 2 * NQ;
+  float4 bc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (has_bc) {  // before the state: its staging waits for it alone
+    const int j = t & (2 * NQ - 1);
+    const float* v = (j < NQ ? a.B : a.C) + (b0 + t / (2 * NQ)) * N;
+    bc = reinterpret_cast<const float4*>(v)[j & (NQ - 1)];
+  }
+
+  struct Row {
+    chunk_t<F> raw;
+    float x, s, z;
+  };
+  uint8_t* const state = static_cast<uint8_t*>(a.state);
+  const int64_t row0 = b0 * a.nheads + ch;
+  auto fetch = [&](int i) {
+    const int64_t row = row0 + static_cast<int64_t>(i) * a.nheads;
+    const int64_t e = row * N + n0;
+    Row r;
+    r.raw = load_stream<chunk_t<F>>(state + chunk_bytes_at<F>(e));
+    r.x = a.x[row];
+    r.s = 1.0f;
+    if constexpr (Traits<F>::scaled) r.s = a.scale[row];
+    r.z = a.z ? a.z[row] : 0.0f;
+    return r;
+  };
+  Row next = fetch(0);
+  float Av[V];
+  load_floats<V>(a.A + static_cast<int64_t>(ch) * N + n0, Av);
+  const float Dv = a.D ? a.D[ch] : 0.0f;
+  if (has_bc) sBC[t] = bc;
+  // The lane's own step sizes, ahead of the loop: inside it, the softplus's double
+  // constants would stay in some thirty registers.
+  __shared__ float sDt[kChannelBatch][256];
+  {
+    const float bias = step_bias(a, ch);
+#pragma unroll 1
+    for (int i = 0; i < nb; ++i)
+      sDt[i][t] = step_size(a, a.dt[row0 + static_cast<int64_t>(i) * a.nheads], bias);
+  }
+  __syncthreads();
+
+#pragma unroll 1
+  for (int i = 0; i < nb; ++i) {
+    const Row cur = next;
+    if (i + 1 < nb) next = fetch(i + 1);
+    const int64_t row = row0 + static_cast<int64_t>(i) * a.nheads;
+    const int64_t e = row * N + n0;
+    const float dtv = sDt[i][t];
+    float hp[V], h[V];
+    decode_chunk<F>(cur.raw, hp);
+    const float dx = dtv * cur.x;
+    const float4* const Bq = sBC + i * 2 * NQ + n0 / 4;
+    float ys = 0.0f;
+#pragma unroll
+    for (int j = 0; j < V / 4; ++j) {
+      float z[4], dA[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) z[u] = dtv * Av[4 * j + u];
+      exp_values_table<4>(sExp, z, dA);
+      const float4 bq = Bq[j], cq = Bq[NQ + j];
+      const float bk[4] = {bq.x, bq.y, bq.z, bq.w};
+      const float ck[4] = {cq.x, cq.y, cq.z, cq.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = 4 * j + u;
+        if constexpr (Traits<F>::scaled) dA[u] = dA[u] * cur.s;  // the old scale folded into the decay
+        h[k] = fmaf(dA[u], hp[k], dx * bk[u]);
+        ys = fmaf(ck[u], h[k], ys);
+      }
+      // Four exponentials in flight: with all of a lane's the registers allow three
+      // waves per SIMD instead of five.
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool bad = !__builtin_isfinite(ys);
+    ys = lane_sum(ys, LR);
+    if (live && cc == 0) a.y[row] = a.z ? (ys + Dv * cur.x) * silu(cur.z) : ys + Dv * cur.x;
+    float rs = 1.0f;
+    if constexpr (Traits<F>::scaled) {
+      float m = 0.0f;
+#pragma unroll
+      for (int k = 0; k < V; ++k) m = fmaxf(m, __builtin_fabsf(h[k]));
+      const float s = group_scale<F>(m);
+      rs = recip_scale(s);
+      if (live) a.scale[row] = s;
+    }
+    const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
+    const chunk_t<F> out =
+        quantize_any<F, R>(h, rs, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), bad);
     if (live) store_stream(state + chunk_bytes_at<F>(e), out);
   }
 }
@@ -853,7 +982,16 @@ static hipError_t launch_rows(const UpdateArgs& a, bool a_per_state, hipStream_t
 }
 
 template <int F, int R>
+static hipError_t launch_channels(const UpdateArgs& a, hipStream_t s) {
+  const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.nheads) * kChannelN / Traits<F>::V + 255) / 256);
+  const unsigned parts = static_cast<unsigned>((a.batch + a.batch_per_wg - 1) / a.batch_per_wg);
+  hipLaunchKernelGGL((k_update_channels<F, R>), dim3(tiles, parts), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+template <int F, int R>
 static hipError_t launch_update_fr(const UpdateArgs& a, int cfg, bool aps, hipStream_t s) {
+  if (cfg == kChannelKernel) return launch_channels<F, R>(a, s);
   return cfg == kRowKernel ? launch_rows<F, R>(a, aps, s) : launch_slab_cfg<F, R>(a, cfg, s);
 }
 

@@ -42,11 +42,13 @@ inline FastDiv make_fastdiv(uint32_t d) {
 // thread) and the row kernel.
 enum UpdateConfig : int {
   kSlab64x4 = 0, kSlab128x4, kSlab256x1, kSlab256x2, kSlab256x4, kSlab512x2, kSlab512x4,
-  kSlab1024x4, kSlab1024x8, kRowKernel
+  kSlab1024x4, kSlab1024x8, kRowKernel, kChannelKernel
 };
 constexpr int kSlabThreads[] = {64, 128, 256, 256, 256, 512, 512, 1024, 1024};
 constexpr int kSlabChunks[] = {4, 4, 1, 2, 4, 2, 4, 4, 8};
 constexpr int kMaxDstate = 1024;  // 64 lanes x 16 E4M3 entries per row
+constexpr int kChannelN = 16;      // channel kernel: entries per row ...
+constexpr int kChannelBatch = 8;   // ... and the most sequences per workgroup
 
 struct UpdateArgs {
   void* state;
@@ -69,6 +71,7 @@ struct UpdateArgs {
   int32_t dstate_shift;     // log2(dstate)
   int32_t group_shift;      // E4M3: log2(entries per scale) when that is a power of two
   int32_t lanes_per_group;  // E4M3: group / 16 lanes; 0 = one scale per head slab
+  int32_t batch_per_wg;     // channel kernel: sequences per workgroup
   int32_t slabs_per_head;   // slab kernels: workgroups per (batch, head) tile
   int64_t head_size;        // headdim * dstate
   int64_t n_chunks;         // total entries / V

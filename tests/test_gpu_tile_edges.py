@@ -80,3 +80,37 @@ def _checkpoint(ssmq, fmt, group, rule, family, shape):
                                          dt.numpy(), A.numpy(), B.numpy(), C.numpy(), D.numpy())
     bar.y(y.check("y").numpy(), wy, y_magnitude(C.numpy(), h_new, D.numpy(), x.numpy(), h // g))
     bar.check()
+
+
+# Mamba-1 layers (rows of 16): a part of a channel tile, a tile and one channel more,
+# and batches whose last workgroup has fewer sequences than the others
+@pytest.mark.parametrize("b,h", [(1, 1), (2, 129), (3, 257), (4099, 9), (6145, 3)])
+@pytest.mark.parametrize("fmt,rule,fused", [("fp16", "weyl", True), ("bf16", "sr", False), ("fp32", "rtn", False),
+                                            ("e4m3", "philox", True), ("int8", "weyl", False), ("int4", "rtn", True)])
+def test_channel_tiles(ssmq, fmt, rule, fused, b, h):
+    say(f"case channels {fmt} {rule} batch {b} channels {h} fused {fused}")
+    group = 16 if fmt in oracle.SCALED else 0
+    A, D = wl.layer_params("mamba1", h, 16, 290)
+    x, dt, B, C = wl.step_inputs(b, h, 1, 16, 1, 291)
+    codes, scale = wl.initial_state(fmt, b, h, 1, 16, 292, group=group)
+    bias = torch.linspace(-3.0, 1.0, h) if fused else None
+    z = torch.randn((b, h, 1), generator=torch.Generator().manual_seed(5)) if fused else None
+    st, y = Guarded(codes), Guarded(torch.zeros(b, h, 1))
+    sc = Guarded(scale) if scale is not None else None
+    dev = {k: None if v is None else v.to(DEV) for k, v in (("dt_bias", bias), ("z", z))}
+    ssmq.state_update(st.t, sc.t if sc else None, x.to(DEV), dt.to(DEV), A.to(DEV), B.to(DEV),
+                      C.to(DEV), D.to(DEV), y.t, rule=rule, fmt=fmt, scale_group=group, step=9,
+                      layer=2, seed=3, entry_base=32, dt_softplus=fused, **dev)
+    torch.cuda.synchronize()
+    r_codes, r_scale, r_y, r_h = oracle.state_update(
+        fmt, rule, wl.to_numpy_codes(fmt, codes), None if scale is None else scale.numpy(), x.numpy(),
+        dt.numpy(), A.numpy(), B.numpy(), C.numpy(), D.numpy(), step=9, layer=2, seed=3, block=16,
+        group=group, entry_base=32, dt_bias=bias.numpy() if fused else None, dt_softplus=fused,
+        z=z.numpy() if fused else None)
+    bar = Bar(fmt, f"channels {fmt} {rule}").codes(wl.to_numpy_codes(fmt, st.check("state")), r_codes)
+    if sc:
+        bar.scales(sc.check("scale").numpy(), r_scale)
+    mag = y_magnitude(C.numpy(), r_h, D.numpy(), x.numpy(), h)
+    if fused:
+        mag = mag * np.abs(torch.nn.functional.silu(z.double()).numpy())
+    bar.y(y.check("y").numpy(), r_y, mag).check()
