@@ -114,3 +114,29 @@ def test_channel_tiles(ssmq, fmt, rule, fused, b, h):
     if fused:
         mag = mag * np.abs(torch.nn.functional.silu(z.double()).numpy())
     bar.y(y.check("y").numpy(), r_y, mag).check()
+
+
+# the 16-byte path of the four-tap convolution (one lane, a wave's and a workgroup's
+# ends) and, one float off alignment or with another width, the general one
+@pytest.mark.parametrize("b,c,width,shift", [(1, 1, 4, 0), (1, 255, 4, 0), (3, 171, 4, 0), (2, 257, 4, 0),
+                                             (2, 257, 4, 1), (2, 257, 3, 0), (2, 257, 5, 0)])
+@pytest.mark.parametrize("act,bias", [(True, True), (False, False)])
+def test_conv1d_paths(ssmq, b, c, width, shift, act, bias):
+    say(f"case conv1d batch {b} channels {c} width {width} shift {shift} act {act}")
+    rng = np.random.default_rng(17)
+    state = rng.standard_normal((b, c, width)).astype(np.float32)
+    x, w = rng.standard_normal((b, c)).astype(np.float32), rng.standard_normal((c, width)).astype(np.float32)
+    bs = rng.standard_normal(c).astype(np.float32) if bias else None
+    room = torch.zeros(state.size + shift)
+    room[shift:] = torch.from_numpy(state.ravel())
+    g, out = Guarded(room), Guarded(torch.zeros(b, c))
+    st = g.t[shift:].view(b, c, width)
+    ssmq.conv1d_update(st, torch.from_numpy(x).to(DEV), torch.from_numpy(w).to(DEV),
+                       None if bs is None else torch.from_numpy(bs).to(DEV), out.t, act=act)
+    torch.cuda.synchronize()
+    r_state, r_out = oracle.conv1d_update(state, x, w, bs, act=act)
+    got = g.check("conv state").numpy()[shift:].reshape(state.shape)
+    assert np.array_equal(got, r_state)
+    # fp32 FMAs in order (width + 1 roundings) and the fp32 silu
+    mag = np.abs(state).max() * np.abs(w).max() * (width + 1) + 4
+    assert np.all(np.abs(out.check("conv out").numpy() - r_out) <= 2.0 ** -22 * mag * (width + 2))
