@@ -1,4 +1,5 @@
-"""Build libssmq.so (the HIP kernels and the C ABI) for gfx950 with hipcc.
+"""Build libssmq.so (the HIP kernels and the C ABI) for gfx950 with hipcc, and the
+CPython module that marshals torch tensors to it (_native.so) with g++.
 
 Floating-point flags matter for parity: no contraction (every product and sum
 is rounded where the source says), IEEE denormals, correctly rounded fp32
@@ -9,12 +10,15 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIBRARY = os.path.join(PKG, "libssmq.so")
+NATIVE = os.path.join(PKG, "_native.so")
+NATIVE_SOURCE = "ssmq_native.cpp"
 SOURCES = ["ssmq_kernels.hip", "ssmq_abi.cpp"]
 ARCH = "gfx950"
 
@@ -35,7 +39,8 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source into libssmq.so; returns the library path."""
+    """Compile every source into libssmq.so and the module beside it; returns the
+    library path."""
     tmp = LIBRARY + ".tmp"
     cmd = [hipcc(), *HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC, "-o", tmp,
            *[os.path.join(CSRC, s) for s in SOURCES]]
@@ -43,7 +48,29 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIBRARY)
+    build_native(verbose)
     return LIBRARY
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compile the CPython module against torch's headers and libssmq.so."""
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(hipcc()))
+    tmp = NATIVE + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(rocm, "include"),
+           os.path.join(CSRC, NATIVE_SOURCE), "-o", tmp, "-L", PKG, "-lssmq",
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, NATIVE)
+    return NATIVE
 
 
 if __name__ == "__main__":
