@@ -28,9 +28,9 @@
 // q is a normal float), X = floor(q24) and U the 24-bit threshold,
 // floor(q + U / 2^24) = (X + U) >> 24 exactly: only the top 24 fraction bits of
 // q can decide the comparison with a multiple of 2^-24. The low byte (nibble)
-// of X + U shifted right by 24 is the stored code. Values are clamped to
-// +-qmax first (the bounds are lattice points, so this is the saturation);
-// NaN and |q| < 2^-126 (q24 then differs from q * 2^24) take the exact path.
+// of X + U shifted right by 24 is the stored code. Values saturate at +-qmax
+// (see quantize_int_chunk); NaN and |q| < 2^-126 (q24 then differs from q * 2^24)
+// take the exact path.
 //
 // Exact software path. Normal ranges use the carry rule on the magnitude bits.
 // Below the smallest normal of fp16 and E4M3 the grid step is fixed, |x| / step
@@ -515,8 +515,18 @@ __device__ inline uint32_t pack_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uin
 
 // INT8 / INT4 chunk of 16 entries. h: the fp32 values, r = fl32(1 / s) and
 // r24 = 2^24 r of their group (r24 is infinite when 2^24 r overflows);
-// maybe_nan: a NaN may be among h. Values are clamped to +-qmax before the
-// floor (the bounds are lattice points, so this is the exact saturation).
+// maybe_nan: a NaN may be among h. Saturation: the group's scale maps its maximum to
+// qmax, so q passes qmax only by rounding, by at most qmax 2^-22.
+//   Round to nearest needs no clamp: such a q still rounds to qmax.
+//   INT8 dithers need none either: X + U then leaves the range of the codes
+//   -127 .. 127 only if U lies within 2^9 of an end of its range, and a sum that has
+//   done so reads, as a signed word, less than -127 2^24. The chunk's smallest sum
+//   (half an instruction per entry) sends those to the exact path.
+//   INT4 dithers clamp to +-qmax before the floor (v_med3_f32, one instruction per
+//   entry; the bounds are lattice points, so this is the exact saturation).
+// One layer of 268M entries in blocks of 128, against a clamp everywhere: INT8 Weyl
+// 119.8 -> 118.1 us, INT8 RTN 97.7 -> 93.9 us, INT4 RTN 81.8 -> 77.6 us.
+constexpr int32_t kInt8Low = -127 * (1 << 24);
 template <int F, int R, typename TG>
 __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, float r24,
                                                const TG& tg, bool maybe_nan) {
@@ -524,25 +534,26 @@ __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, f
   uint32_t S[16];
   bool rare = maybe_nan;
   if constexpr (R == kRTN) {
-    // Adding 1.5 * 2^23 rounds the clamped q to an integer, ties to even (the
-    // sum's ulp is 1), and leaves that integer's two's complement in the low
-    // bits of the sum's encoding.
+    // Adding 1.5 * 2^23 rounds q to an integer, ties to even (the sum's ulp is 1),
+    // and leaves that integer's two's complement in the low bits of the sum's
+    // encoding. (NaN, from an infinite group maximum, leaves 0.)
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-      S[k] = __float_as_uint(__builtin_amdgcn_fmed3f(h[k] * r, -qmax, qmax) + 0x1.8p23f);
+    for (int k = 0; k < 16; ++k) S[k] = __float_as_uint(h[k] * r + 0x1.8p23f);
   } else {
     float mn = __builtin_inff();
+    int32_t low = 0;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const float q24 = h[k] * r24;
       mn = fminf(mn, __builtin_fabsf(q24));
-      int X;  // floor of the clamped value
-      asm("v_cvt_flr_i32_f32 %0, %1"
-          : "=v"(X)
-          : "v"(__builtin_amdgcn_fmed3f(q24, -qmax * 0x1p24f, qmax * 0x1p24f)));
+      float c24 = q24;
+      if constexpr (F == kINT4) c24 = __builtin_amdgcn_fmed3f(q24, -qmax * 0x1p24f, qmax * 0x1p24f);
+      int X;  // floor
+      asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(X) : "v"(c24));
       S[k] = static_cast<uint32_t>(X) + (tg(k) >> 8);
+      if constexpr (F == kINT8) low = min(low, static_cast<int32_t>(S[k]));
     }
-    rare = rare || !(mn >= 0x1p-102f) || !(r24 < __builtin_inff());
+    rare = rare || !(mn >= 0x1p-102f) || !(r24 < __builtin_inff()) || low < kInt8Low;
   }
   constexpr int B = (R == kRTN) ? 0 : 3;  // the byte that holds the code
   uint32_t w[4];
@@ -567,8 +578,10 @@ __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, f
       if constexpr (R == kRTN) {
         exact = h[k] != h[k];
       } else {
-        // NaN, q below the normal range (q24 then differs from q 2^24), or r24 overflowed
-        exact = !(__builtin_fabsf(h[k] * r24) >= 0x1p-102f) || !(r24 < __builtin_inff());
+        // NaN, q below the normal range (q24 then differs from q 2^24), r24 overflowed, or
+        // an INT8 sum out of the codes' range
+        exact = !(__builtin_fabsf(h[k] * r24) >= 0x1p-102f) || !(r24 < __builtin_inff()) ||
+                (F == kINT8 && static_cast<int32_t>(S[k]) < kInt8Low);
       }
       if (exact) patch_code<F>(w, k, round_code<F, R>(h[k] * r, tg(k)));
     }
