@@ -295,6 +295,7 @@ ssmq_status ssmq_requantize(const ssmq_qparams* q, int64_t n_entries, int64_t he
   a.thr = make_thr(q->rule, q->seed, q->layer, q->step, q->dither_block, a.toff);
   a.lanes_per_group = 64;
   if (scaled && group / 16 <= 64 && is_pow2(group / 16)) a.lanes_per_group = static_cast<int32_t>(group / 16);
+  a.lpg_shift = log2i(a.lanes_per_group);
   if (!scaled && (n_entries + 16 * 256 - 1) / (16 * 256) > 0x7FFFFFFFLL)
     return fail(SSMQ_EUNSUPPORTED, "too many entries for one launch");
   hipError_t e = ssmq::launch_requant(a, q->format, q->rule, static_cast<hipStream_t>(stream));

@@ -359,10 +359,12 @@ struct FpSpan {
   int64_t first;    // the wave's first unit
   int64_t units;    // units of the state from that one on (<= 0: a wave past its end)
   int lane;
+  __device__ FpSpan(uint4* block_lds, void* state, int64_t first_unit, int64_t end_unit, int t)
+      : lds(block_lds + (t >> 6) * 64 * S), state(static_cast<uint8_t*>(state)), first(first_unit),
+        units(end_unit - first_unit), lane(t & 63) {}
   __device__ FpSpan(uint4* block_lds, const UpdateArgs& a, int t)
-      : lds(block_lds + (t >> 6) * 64 * S), state(static_cast<uint8_t*>(a.state)),
-        first((static_cast<int64_t>(blockIdx.x) * 256 + (t & ~63)) * S),
-        units(a.n_chunks * S - first), lane(t & 63) {}
+      : FpSpan(block_lds, a.state, (static_cast<int64_t>(blockIdx.x) * 256 + (t & ~63)) * S,
+               a.n_chunks * S, t) {}
   __device__ static int at(int owner, int k) {
     return owner * S + (k ^ ((owner >> (S == 4 ? 1 : 2)) & (S - 1)));
   }
@@ -373,13 +375,19 @@ struct FpSpan {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  __device__ void load(float (&v)[V]) {
-    uint4 u[S];
+  __device__ void fetch(uint4 (&u)[S]) const {
 #pragma unroll
     for (int i = 0; i < S; ++i) {  // past the end (a ragged last block) the state's first unit is read
       const int n = i * 64 + lane;
       u[i] = load_stream<uint4>(state + (n < units ? (first + n) * 16 : 0));
     }
+  }
+  __device__ void load(float (&v)[V]) {
+    uint4 u[S];
+    fetch(u);
+    distribute(u, v);
+  }
+  __device__ void distribute(const uint4 (&u)[S], float (&v)[V]) {
 #pragma unroll
     for (int i = 0; i < S; ++i) {
       const int n = i * 64 + lane;
@@ -631,19 +639,27 @@ __device__ inline void store_code(void* codes, int64_t k, uint32_t c) {
   else static_cast<uint8_t*>(codes)[k] = static_cast<uint8_t>(c);
 }
 
+// The fp32 entries of the 16-bit formats come through LDS in whole lines (see FpSpan):
+// bf16, 63M entries (377 MB) 64.3 -> 62.5 us.
 template <int F, int R>
 __global__ __launch_bounds__(256) void k_requant(RequantArgs a) {
   constexpr int V = Traits<F>::V;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t e = q * V;
+  float h[V];
+  __shared__ uint4 sSpan[V > 4 ? 256 * (V / 4) : 1];
+  if constexpr (V > 4) {
+    // Units up to the last whole one: a lane with a whole chunk has all of its own.
+    FpSpan<V> span(sSpan, const_cast<float*>(a.h), (q & ~int64_t{63}) * (V / 4), a.n / 4, threadIdx.x);
+    if (a.n >= 4) span.load(h);
+  }
   if (e >= a.n) return;
   const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
   if (e + V <= a.n) {
-    float h[V];
-    load_floats<V>(a.h + e, h);
+    if constexpr (V == 4) load_floats<V>(a.h + e, h);
     const uint4 out = quantize_chunk<F, R>(h, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff),
                                            chunk_has_nan<V>(h));
-    *reinterpret_cast<uint4*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
+    *reinterpret_cast<chunk_t<F>*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
   } else {
     for (int64_t k = e; k < a.n; ++k) {
       const uint64_t gk = a.entry_base + static_cast<uint64_t>(k);
@@ -699,37 +715,70 @@ __global__ __launch_bounds__(256) void k_requant_scaled(RequantArgs a) {
   }
 }
 
-// Groups of 256 * 16 * CPT entries (4096 or 8192, e.g. one scale per 64x128
-// head): one workgroup per group, its values held in registers between the
-// maximum and the rounding, so the fp32 input is read once.
-template <int F, int R, int CPT>
-__global__ __launch_bounds__(256) void k_requant_group_wg(RequantArgs a) {
+// Groups of up to 64 chunks (a power of two): one chunk per lane, held in registers
+// between the maximum and the rounding, so the fp32 input is read once. It comes
+// through LDS in whole lines (see FpSpan). 63M entries against two strided reads (5 bytes
+// each): INT8 blocks of 128, hash SR 62.6 -> 54.2 us; INT4 blocks of 16, RTN 59.4 -> 50.3 us.
+template <int F, int R>
+__global__ __launch_bounds__(256) void k_requant_chunks(RequantArgs a) {
   const int t = threadIdx.x;
-  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * a.group;
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + t;
+  __shared__ uint4 sSpan[256 * 4];
+  FpSpan<16> span(sSpan, const_cast<float*>(a.h), (q & ~int64_t{63}) * 4, a.n / 4, t);
+  float h[16];
+  span.load(h);
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[k]));
+  const float s = group_scale<F>(__uint_as_float(lane_umax(__float_as_uint(m), a.lanes_per_group)));
+  const float rs = recip_scale(s);
+  const bool live = q * 16 < a.n;  // whole groups are live or dead together
+  const int64_t e = live ? q * 16 : 0;
+  if (live && (t & (a.lanes_per_group - 1)) == 0) a.scale[q >> a.lpg_shift] = s;
+  const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
+  const chunk_t<F> out = quantize_any<F, R>(
+      h, rs, chunk_thr<R, 16>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), chunk_has_nan<16>(h));
+  if (live) *reinterpret_cast<chunk_t<F>*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
+}
+
+// Groups of NT * 16 * CPT entries (e.g. one scale per 64x128 head): one workgroup per
+// group, its values held in registers between the maximum and the rounding. Bound by HBM:
+// each load of a wave covers 1 KiB without gaps and reaches its lane through LDS (E4M3,
+// 63M entries, 315 MB: heads of 8192 entries 55.9 -> 54.9 us; heads of 16384, which one
+// wave each read twice, 51.1 -> 27.5 us for half as many).
+template <int F, int R, int NT, int CPT>
+__global__ __launch_bounds__(NT) void k_requant_group_wg(RequantArgs a) {
+  const int t = threadIdx.x;
+  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * (NT * CPT);  // the group's first chunk
+  const int64_t e0 = c0 * 16;
+  __shared__ uint4 sSpan[NT * 4];
+  FpSpan<16> span(sSpan, const_cast<float*>(a.h), (c0 + (t & ~63)) * 4, a.n / 4, t);
+  uint4 u[CPT][4];
+#pragma unroll
+  for (int j = 0; j < CPT; ++j, span.first += NT * 4, span.units -= NT * 4) span.fetch(u[j]);
   float h[CPT][16];
   float m = 0.0f;
 #pragma unroll
   for (int j = 0; j < CPT; ++j) {
-    load_floats<16>(a.h + e0 + (static_cast<int64_t>(j) * 256 + t) * 16, h[j]);
+    span.distribute(u[j], h[j]);
+    if (j + 1 < CPT) span.wave_sync();  // its units have been read before the next ones replace them
 #pragma unroll
     for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[j][k]));
   }
-  __shared__ uint32_t red[4];
-  __shared__ float rsh;
+  constexpr int NW = NT / 64;
+  __shared__ uint32_t red[NW];
   const uint32_t mw = lane_umax(__float_as_uint(m), 64);
   if ((t & 63) == 0) red[t >> 6] = mw;
   __syncthreads();
-  if (t == 0) {
-    const uint32_t w = max(max(red[0], red[1]), max(red[2], red[3]));
-    const float sc = group_scale<F>(__uint_as_float(w));
-    a.scale[blockIdx.x] = sc;
-    rsh = recip_scale(sc);
-  }
-  __syncthreads();
-  const float rs = rsh;
+  uint32_t w = red[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) w = max(w, red[i]);
+  const float s = group_scale<F>(__uint_as_float(w));
+  const float rs = recip_scale(s);
+  if (t == 0) a.scale[blockIdx.x] = s;
 #pragma unroll
   for (int j = 0; j < CPT; ++j) {
-    const int64_t e = e0 + (static_cast<int64_t>(j) * 256 + t) * 16;
+    const int64_t e = e0 + (static_cast<int64_t>(j) * NT + t) * 16;
     const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
     const chunk_t<F> out = quantize_any<F, R>(
         h[j], rs, chunk_thr<R, 16>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), chunk_has_nan<16>(h[j]));
@@ -1051,14 +1100,26 @@ static hipError_t launch_requant_f(const RequantArgs& a, int rule, hipStream_t s
   return hipGetLastError();
 }
 
-template <int F, int CPT>
+template <int F, int NT, int CPT>
 static hipError_t launch_requant_group_wg(const RequantArgs& a, int rule, hipStream_t s) {
   const unsigned grid = static_cast<unsigned>(a.n / a.group);
   switch (rule) {
-    case kRTN: hipLaunchKernelGGL((k_requant_group_wg<F, kRTN, CPT>), dim3(grid), dim3(256), 0, s, a); break;
-    case kSR: hipLaunchKernelGGL((k_requant_group_wg<F, kSR, CPT>), dim3(grid), dim3(256), 0, s, a); break;
-    case kPHILOX: hipLaunchKernelGGL((k_requant_group_wg<F, kPHILOX, CPT>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_requant_group_wg<F, kWEYL, CPT>), dim3(grid), dim3(256), 0, s, a); break;
+    case kRTN: hipLaunchKernelGGL((k_requant_group_wg<F, kRTN, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_requant_group_wg<F, kSR, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_requant_group_wg<F, kPHILOX, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_requant_group_wg<F, kWEYL, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
+  }
+  return hipGetLastError();
+}
+
+template <int F>
+static hipError_t launch_requant_chunks(const RequantArgs& a, int rule, hipStream_t s) {
+  const unsigned grid = static_cast<unsigned>((a.n / 16 + 255) / 256);
+  switch (rule) {
+    case kRTN: hipLaunchKernelGGL((k_requant_chunks<F, kRTN>), dim3(grid), dim3(256), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_requant_chunks<F, kSR>), dim3(grid), dim3(256), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_requant_chunks<F, kPHILOX>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_requant_chunks<F, kWEYL>), dim3(grid), dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }
@@ -1066,9 +1127,18 @@ static hipError_t launch_requant_group_wg(const RequantArgs& a, int rule, hipStr
 template <int F>
 static hipError_t launch_requant_scaled(const RequantArgs& a, int rule, hipStream_t s) {
   const int64_t n_groups = a.n / a.group;
-  if (n_groups <= 0x7FFFFFFFLL) {
-    if (a.group == 4096) return launch_requant_group_wg<F, 1>(a, rule, s);
-    if (a.group == 8192) return launch_requant_group_wg<F, 2>(a, rule, s);
+  // One read of the input where a group fits a wave or a workgroup; launches of 2^32
+  // threads or more and the other groups take the loop over groups.
+  if (a.n / 16 < 0xFFFFFF00LL) {
+    if (a.group <= 1024 && a.lanes_per_group * 16 == a.group) return launch_requant_chunks<F>(a, rule, s);
+    switch (a.group) {
+      case 2048: return launch_requant_group_wg<F, 128, 1>(a, rule, s);
+      case 4096: return launch_requant_group_wg<F, 256, 1>(a, rule, s);
+      case 8192: return launch_requant_group_wg<F, 256, 2>(a, rule, s);
+      case 16384: return launch_requant_group_wg<F, 256, 4>(a, rule, s);
+      case 32768: return launch_requant_group_wg<F, 512, 4>(a, rule, s);
+      default: break;
+    }
   }
   const int64_t gpw = 64 / a.lanes_per_group;
   int64_t blocks = (n_groups + 4 * gpw - 1) / (4 * gpw);

@@ -140,3 +140,26 @@ def test_conv1d_paths(ssmq, b, c, width, shift, act, bias):
     # fp32 FMAs in order (width + 1 roundings) and the fp32 silu
     mag = np.abs(state).max() * np.abs(w).max() * (width + 1) + 4
     assert np.all(np.abs(out.check("conv out").numpy() - r_out) <= 2.0 ** -22 * mag * (width + 2))
+
+
+# entries of a part of a chunk, of a wave and one chunk more, of a workgroup and a
+# ragged end; scale groups of one lane, of a wave, of a workgroup of each size
+@pytest.mark.parametrize("fmt,rule,group,n", [
+    ("fp16", "weyl", 0, 3), ("bf16", "sr", 0, 13), ("fp16", "rtn", 0, 520), ("bf16", "weyl", 0, 2051),
+    ("fp16", "philox", 0, 4101), ("int8", "weyl", 16, 16 * 65), ("int4", "sr", 128, 128 * 33),
+    ("e4m3", "weyl", 1024, 1024 * 5), ("int8", "rtn", 2048, 2048 * 3), ("e4m3", "philox", 4096, 4096),
+    ("int4", "weyl", 8192, 8192 * 2), ("e4m3", "sr", 16384, 16384 * 3), ("int8", "weyl", 32768, 32768 * 2)])
+def test_requantize_spans(ssmq, fmt, rule, group, n):
+    say(f"case requantize span {fmt} {rule} g{group} n {n}")
+    x = (np.random.default_rng(n).standard_normal(n) * 0.3).astype(np.float32)
+    per = 2 if fmt == "int4" else 1
+    codes = Guarded(torch.zeros(n // per, dtype=wl.CODE_TORCH_DTYPE[fmt]))
+    sc = Guarded(torch.zeros(n // group)) if group else None
+    ssmq.requantize(Guarded(torch.from_numpy(x)).t, codes.t, sc.t if sc else None, rule=rule, fmt=fmt,
+                    scale_group=group, seed=2, layer=3, step=9, dither_block=16)
+    torch.cuda.synchronize()
+    want, wsc = oracle.requantize(fmt, rule, x, seed=2, layer=3, step=9, block=16, group=group)
+    got = wl.to_numpy_codes(fmt, codes.check("codes"))
+    assert np.array_equal(got.ravel(), np.asarray(want).ravel())
+    if sc:
+        assert np.array_equal(sc.check("scale").numpy(), wsc)
