@@ -744,7 +744,7 @@ __global__ __launch_bounds__(256) void k_requant_chunks(RequantArgs a) {
 // Groups of NT * 16 * CPT entries (e.g. one scale per 64x128 head): one workgroup per
 // group, its values held in registers between the maximum and the rounding. Bound by HBM:
 // each load of a wave covers 1 KiB without gaps and reaches its lane through LDS (E4M3,
-// 63M entries, 315 MB: heads of 8192 entries 55.9 -> 54.9 us; heads of 16384, which one
+// 63M entries, 315 MB: heads of 8192 entries 55.5 -> 50.6 us; heads of 16384, which one
 // wave each read twice, 51.1 -> 27.5 us for half as many).
 template <int F, int R, int NT, int CPT>
 __global__ __launch_bounds__(NT) void k_requant_group_wg(RequantArgs a) {
@@ -820,139 +820,172 @@ __global__ __launch_bounds__(256) void k_dither_fill(DitherArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Open-loop replay. Thread q owns entries 4q .. 4q+3 for all steps: the fp32
+// Open-loop replay. Thread q owns entries E q .. E q + E - 1 for all steps: the fp32
 // reference h and the stored value hq stay in registers, so the only traffic is
-// the trace (a and w, 8 bytes per entry and step, nontemporal, the next step's
-// rows loaded while the current one is rounded) and the error sums per block.
+// the trace (a and w, 8 bytes per entry and step, nontemporal, the rows of the next
+// AHEAD steps loaded while the current one is rounded) and the error sums per block.
 // Each step rounds fma(a, hq, w) with the exact software rounding of the
 // format (the per-entry functions of the fused kernels' exact path); the
 // scaled formats first reduce max|x| over the group's lanes. Lanes past n
-// (the grid's ragged end) run with zero inputs and store nothing, so the group
+// (the grid's ragged end) run on the first entries and store nothing, so the group
 // reductions always see whole groups.
+//
+// Four entries per thread and one step ahead stream a long state at the rate of HBM (1.3M
+// entries, 256 steps: 485 us, 5.7 TB/s; two or four steps ahead, with more rows open at
+// once, 505 and 530 us). A state below kReplayShort entries then has less than two waves
+// per SIMD, and the steps' own chain of dependent operations and loads sets the pace:
+// two entries per thread, four steps ahead, in workgroups of one wave give it twice the
+// waves on more CUs. INT8, 12k entries 145 -> 99 us; fp16, 147k 139 -> 88 us; INT8, 328k
+// (300 steps) 214 -> 169 us; bf16, 655k 300 -> 295 us, but INT8, 983k 372 -> 408 us.
 // ---------------------------------------------------------------------------
-template <int F, int R>
+constexpr int64_t kReplayShort = 1 << 19;
+
+// Two or four 32-bit words in one access.
+template <int E>
+__device__ inline void load_words(const float* p, float (&v)[E]) {
+  typedef unsigned int words __attribute__((ext_vector_type(E)));
+  const words w = __builtin_nontemporal_load(reinterpret_cast<const words*>(p));
+#pragma unroll
+  for (int k = 0; k < E; ++k) v[k] = __uint_as_float(w[k]);
+}
+template <int W>
+__device__ inline void store_words(uint32_t* p, const uint32_t (&v)[W]) {
+  typedef unsigned int words __attribute__((ext_vector_type(W)));
+  words w;
+#pragma unroll
+  for (int k = 0; k < W; ++k) w[k] = v[k];
+  *reinterpret_cast<words*>(p) = w;
+}
+
+template <int F, int R, int E>
 __device__ inline void replay_round(const ReplayArgs& a, uint64_t e0, uint32_t step,
-                                    const float (&x)[4], float (&hq)[4], uint32_t (&code)[4],
+                                    const float (&x)[E], float (&hq)[E], uint32_t (&code)[E],
                                     float& scale) {
   Thr th = a.thr;
   th.step = step;
   if constexpr (R == kWEYL) th.key = a.weyl_key0 + kWeylPhi * (step - a.step0);
   else if constexpr (R == kSR) th.key = sr_step_key(a.sr_key0, step);
-  uint32_t thr[4];
+  uint32_t thr[E];
   if constexpr (R == kPHILOX) {
     const ChunkThr<R, 4> t4 = chunk_thr<R, 4>(e0, th, 0u, nullptr);
+    const bool upper = E == 2 && (e0 & 2u) != 0;  // entries 2 and 3 of the block of four
 #pragma unroll
-    for (int k = 0; k < 4; ++k) thr[k] = t4(k);
+    for (int k = 0; k < E; ++k) thr[k] = upper ? t4(k + 4 - E) : t4(k);
   } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) thr[k] = entry_thr<R>(e0 + k, th);
+    for (int k = 0; k < E; ++k) thr[k] = entry_thr<R>(e0 + k, th);
   }
   if constexpr (Traits<F>::scaled) {
     float m = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m = fmaxf(m, __builtin_fabsf(x[k]));
+    for (int k = 0; k < E; ++k) m = fmaxf(m, __builtin_fabsf(x[k]));
     const float s = group_scale<F>(__uint_as_float(lane_umax(__float_as_uint(m), a.lanes_per_group)));
     const float r = recip_scale(s);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < E; ++k) {
       code[k] = round_code<F, R>(x[k] * r, thr[k]);
       hq[k] = code_value<F>(code[k]) * s;
     }
     scale = s;
   } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < E; ++k) {
       code[k] = round_code<F, R>(x[k], thr[k]);
       hq[k] = code_value<F>(code[k]);
     }
   }
 }
 
-template <int F, int R>
+template <int F, int R, int E, int AHEAD>
 __global__ __launch_bounds__(256) void k_replay(ReplayArgs a) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t i0 = q * 4;
-  const bool live = i0 < a.n;
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const bool live = q * E < a.n;
+  const int64_t i0 = live ? q * E : 0;
   const uint64_t e0 = a.entry_base + static_cast<uint64_t>(i0);
-  float h[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (live) load_floats<4>(a.h0 + i0, h);
-  float hq[4];
-  uint32_t code[4];
+  float h[E];
+  load_words(a.h0 + i0, h);
+  float hq[E];
+  uint32_t code[E];
   float scale = 0.0f;
-  replay_round<F, R>(a, e0, a.step0, h, hq, code, scale);
+  replay_round<F, R, E>(a, e0, a.step0, h, hq, code, scale);
 
-  double err[4] = {0.0, 0.0, 0.0, 0.0}, ref[4] = {0.0, 0.0, 0.0, 0.0};
-  float an[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (live && a.steps > 0) {
-    const uint4 av = load_stream<uint4>(a.a + i0), wv = load_stream<uint4>(a.w + i0);
-    an[0] = __uint_as_float(av.x); an[1] = __uint_as_float(av.y);
-    an[2] = __uint_as_float(av.z); an[3] = __uint_as_float(av.w);
-    wn[0] = __uint_as_float(wv.x); wn[1] = __uint_as_float(wv.y);
-    wn[2] = __uint_as_float(wv.z); wn[3] = __uint_as_float(wv.w);
-  }
-  for (int32_t t = 1; t <= a.steps; ++t) {
-    float at[4], wt[4];
+  double err[E] = {}, ref[E] = {};
+  float an[AHEAD][E] = {}, wn[AHEAD][E] = {};
+  const uint32_t steps = static_cast<uint32_t>(a.steps);
+  auto fetch = [&](uint32_t t, int u) {
+    const int64_t off = static_cast<int64_t>(t) * a.n + i0;
+    load_words(a.a + off, an[u]);
+    load_words(a.w + off, wn[u]);
+  };
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { at[k] = an[k]; wt[k] = wn[k]; }
-    if (live && t < a.steps) {  // the next step's rows, in flight while this one rounds
-      const int64_t off = static_cast<int64_t>(t) * a.n + i0;
-      const uint4 av = load_stream<uint4>(a.a + off), wv = load_stream<uint4>(a.w + off);
-      an[0] = __uint_as_float(av.x); an[1] = __uint_as_float(av.y);
-      an[2] = __uint_as_float(av.z); an[3] = __uint_as_float(av.w);
-      wn[0] = __uint_as_float(wv.x); wn[1] = __uint_as_float(wv.y);
-      wn[2] = __uint_as_float(wv.z); wn[3] = __uint_as_float(wv.w);
-    }
-    float x[4];
+  for (int u = 0; u < AHEAD; ++u)
+    if (static_cast<uint32_t>(u) < steps) fetch(u, u);
+  int32_t left = a.block_steps;  // steps until the block's sums are stored
+  int64_t out = i0;
+  auto step = [&](uint32_t t, int u) {  // step t + 1, whose row is in slot u
+    float at[E], wt[E];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < E; ++k) { at[k] = an[u][k]; wt[k] = wn[u][k]; }
+    if (t + AHEAD < steps) fetch(t + AHEAD, u);  // in flight while this step rounds
+    float x[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
       h[k] = fmaf(at[k], h[k], wt[k]);
       x[k] = fmaf(at[k], hq[k], wt[k]);
     }
-    replay_round<F, R>(a, e0, a.step0 + static_cast<uint32_t>(t), x, hq, code, scale);
+    replay_round<F, R, E>(a, e0, a.step0 + t + 1u, x, hq, code, scale);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < E; ++k) {
       const double d = static_cast<double>(hq[k]) - static_cast<double>(h[k]);
       err[k] += d * d;
       ref[k] += static_cast<double>(h[k]) * static_cast<double>(h[k]);
     }
-    if (t % a.block_steps == 0 || t == a.steps) {
+    if (--left == 0 || t + 1 == steps) {
       if (live) {
-        const int64_t off = static_cast<int64_t>((t - 1) / a.block_steps) * a.n + i0;
-        double2* pe = reinterpret_cast<double2*>(a.err + off);
-        pe[0] = make_double2(err[0], err[1]);
-        pe[1] = make_double2(err[2], err[3]);
-        if (a.ref) {
-          double2* pr = reinterpret_cast<double2*>(a.ref + off);
-          pr[0] = make_double2(ref[0], ref[1]);
-          pr[1] = make_double2(ref[2], ref[3]);
+#pragma unroll
+        for (int k = 0; k < E; k += 2) {
+          *reinterpret_cast<double2*>(a.err + out + k) = make_double2(err[k], err[k + 1]);
+          if (a.ref) *reinterpret_cast<double2*>(a.ref + out + k) = make_double2(ref[k], ref[k + 1]);
         }
       }
+      out += a.n;
+      left = a.block_steps;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { err[k] = 0.0; ref[k] = 0.0; }
+      for (int k = 0; k < E; ++k) { err[k] = 0.0; ref[k] = 0.0; }
     }
+  };
+#pragma unroll 1
+  for (uint32_t t = 0; t < steps; t += AHEAD) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (t + u < steps) step(t + u, u);
   }
   if (!live) return;
   if (a.codes) {
-    if constexpr (F == kFP32) {
-      *reinterpret_cast<uint4*>(static_cast<uint32_t*>(a.codes) + i0) =
-          make_uint4(code[0], code[1], code[2], code[3]);
-    } else if constexpr (F == kBF16 || F == kFP16) {
-      *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.codes) + i0) =
-          make_uint2(code[0] | (code[1] << 16), code[2] | (code[3] << 16));
-    } else if constexpr (F == kINT4) {
-      static_cast<uint16_t*>(a.codes)[i0 / 4] =
-          static_cast<uint16_t>(code[0] | (code[1] << 4) | (code[2] << 8) | (code[3] << 12));
+    constexpr int bits = Traits<F>::CB * 8 / Traits<F>::V;  // code width
+    if constexpr (bits * E >= 32) {
+      uint32_t w[bits * E / 32] = {};
+#pragma unroll
+      for (int k = 0; k < E; ++k) w[k * bits / 32] |= code[k] << (k * bits % 32);
+      store_words(static_cast<uint32_t*>(a.codes) + i0 / E * (bits * E / 32), w);
     } else {
-      static_cast<uint32_t*>(a.codes)[i0 / 4] =
-          code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
+      uint32_t w = 0;
+#pragma unroll
+      for (int k = 0; k < E; ++k) w |= code[k] << (k * bits);
+      if constexpr (bits * E == 16) static_cast<uint16_t*>(a.codes)[i0 / E] = static_cast<uint16_t>(w);
+      else static_cast<uint8_t*>(a.codes)[i0 / E] = static_cast<uint8_t>(w);
     }
   }
   if constexpr (Traits<F>::scaled) {
     if (a.scale && (threadIdx.x & (a.lanes_per_group - 1)) == 0)
       a.scale[static_cast<int64_t>(e0 - a.entry_base) >> a.group_shift] = scale;
   }
-  if (a.h_final)
-    *reinterpret_cast<float4*>(a.h_final + i0) = make_float4(h[0], h[1], h[2], h[3]);
+  if (a.h_final) {
+    uint32_t w[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) w[k] = __float_as_uint(h[k]);
+    store_words(reinterpret_cast<uint32_t*>(a.h_final) + i0, w);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1176,16 +1209,26 @@ hipError_t launch_dither(const DitherArgs& a, int rule, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int F>
-static hipError_t launch_replay_f(const ReplayArgs& a, int rule, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>((a.n / 4 + 255) / 256);
+template <int F, int E, int AHEAD>
+static hipError_t launch_replay_e(const ReplayArgs& a, int rule, int threads, hipStream_t s) {
+  const unsigned grid = static_cast<unsigned>((a.n / E + threads - 1) / threads);
   switch (rule) {
-    case kRTN: hipLaunchKernelGGL((k_replay<F, kRTN>), dim3(grid), dim3(256), 0, s, a); break;
-    case kSR: hipLaunchKernelGGL((k_replay<F, kSR>), dim3(grid), dim3(256), 0, s, a); break;
-    case kPHILOX: hipLaunchKernelGGL((k_replay<F, kPHILOX>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_replay<F, kWEYL>), dim3(grid), dim3(256), 0, s, a); break;
+    case kRTN: hipLaunchKernelGGL((k_replay<F, kRTN, E, AHEAD>), dim3(grid), dim3(threads), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_replay<F, kSR, E, AHEAD>), dim3(grid), dim3(threads), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_replay<F, kPHILOX, E, AHEAD>), dim3(grid), dim3(threads), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_replay<F, kWEYL, E, AHEAD>), dim3(grid), dim3(threads), 0, s, a); break;
   }
   return hipGetLastError();
+}
+
+template <int F>
+static hipError_t launch_replay_f(const ReplayArgs& a, int rule, hipStream_t s) {
+  if (a.n < kReplayShort && a.lanes_per_group <= 32) {  // groups of 256 entries need four per lane
+    ReplayArgs b = a;
+    if (Traits<F>::scaled) b.lanes_per_group *= 2;
+    return launch_replay_e<F, 2, 4>(b, rule, 64, s);
+  }
+  return launch_replay_e<F, 4, 1>(a, rule, 256, s);
 }
 
 hipError_t launch_replay(const ReplayArgs& a, int format, int rule, hipStream_t s) {

@@ -116,7 +116,7 @@ struct DitherArgs {
   Thr thr;
 };
 
-// Open-loop replay of recorded decays and writes: four entries per thread.
+// Open-loop replay of recorded decays and writes.
 struct ReplayArgs {
   const float* h0;          // [n]
   const float* a;           // [steps][n]
@@ -128,7 +128,7 @@ struct ReplayArgs {
   float* h_final;           // final reference state or null
   int64_t n;                // entries, a multiple of 4
   int32_t steps, block_steps;
-  int32_t lanes_per_group;  // scaled formats: group / 4, a power of two <= 64
+  int32_t lanes_per_group;  // scaled formats: group / entries per thread (4 until launched), a power of two <= 64
   int32_t group_shift;      // log2(group)
   uint64_t entry_base;      // a multiple of 4
   uint32_t step0;           // step of the write of h0

@@ -135,3 +135,18 @@ def test_replay_full_layer_sampled(ssmq):
         assert np.array_equal(err[:, sl], want["err"])
         assert np.array_equal(codes[sl], want["codes"])
         assert np.array_equal(scale[lo // 16:(lo + 4096) // 16], want["scale"])
+
+
+# short states take two entries per lane, four steps ahead; long ones four per lane
+@pytest.mark.parametrize("fmt,group,rule,n,T", [
+    ("int4", 4, "philox", 4, 1), ("fp16", 0, "philox", 12, 4), ("int8", 16, "sr", 16 * 9, 5),
+    ("e4m3", 128, "weyl", 128 * 3, 8), ("fp32", 0, "rtn", 132, 3),
+    ("int4", 16, "weyl", 2 ** 19 - 16, 2), ("fp16", 0, "sr", 2 ** 19 + 12, 3),
+    ("bf16", 0, "philox", 2 ** 19, 2), ("e4m3", 16, "philox", 2 ** 19 + 48, 3),
+    ("int4", 4, "sr", 2 ** 19 + 4, 2), ("fp32", 0, "weyl", 2 ** 19 + 1024, 1)])
+def test_replay_lengths(ssmq, fmt, group, rule, n, T):
+    h0, a, w = _traces(n, T, seed=n % 1000)
+    say(f"case replay {fmt} {rule} group {group}: n {n}, T {T}")
+    got, want = _run(ssmq, fmt, rule, h0, a, w, group, 3, dither_block=16, seed=1, layer=2, step=9,
+                     entry_base=32)
+    _same(got, want, (fmt, rule, n))
