@@ -64,20 +64,20 @@ __device__ inline float silu(float v) { return v / (1.0f + expf(-v)); }
 // 128-register line; they are held to it (four waves per SIMD) instead of
 // dropping to three waves.
 //
-// N128: the state dimension is 128 and a scale group is 128 entries (8 lanes)
-// or the whole head, so the lanes per row and per group are compile-time
-// constants: the reductions lose their runtime width tests (INT8 / INT4 about
-// 6 % faster).
+// LR > 0: a row is LR lanes and a scale group one row or the whole head, so the lanes
+// per row and per group are compile-time constants: the reductions lose their runtime
+// width tests. 44M entries, one group per row: 64x256 heads INT8 Weyl 25.6 -> 22.6 us, RTN
+// 22.1 -> 18.3 us; 32x256 INT4 RTN 18.0 -> 14.3 us; 128x64 INT8 Weyl 23.9 -> 21.7 us.
 constexpr int log2c(int v) { return v <= 1 ? 0 : 1 + log2c(v / 2); }
 
-template <int F, int R, int NT, int CPT, bool N128 = false>
+template <int F, int R, int NT, int CPT, int LR = 0>
 __global__ __launch_bounds__(NT, (Traits<F>::scaled && CPT == 4 && NT <= 128) ? 4 : 1)
 void k_update_slab(UpdateArgs a) {
   constexpr int V = Traits<F>::V;
   constexpr int NW = NT / 64;
-  const int lanes_per_row = N128 ? 128 / V : a.lanes_per_row;
-  const int lr_shift = N128 ? log2c(128 / V) : a.lr_shift;
-  const int lanes_per_group = N128 ? 8 : a.lanes_per_group;  // when not the whole head
+  const int lanes_per_row = LR ? LR : a.lanes_per_row;
+  const int lr_shift = LR ? log2c(LR) : a.lr_shift;
+  const int lanes_per_group = LR ? LR : a.lanes_per_group;  // when not the whole head
   const int t = threadIdx.x;
   const uint32_t blk = blockIdx.x;
   const uint32_t tile32 = a.div_slabs.div(blk);  // b * nheads + h
@@ -1031,36 +1031,48 @@ __global__ __launch_bounds__(256) void k_conv1d_update(ConvArgs a) {
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-template <int F, int R, int NT, int CPT, bool N128 = false>
+template <int F, int R, int NT, int CPT, int LR = 0>
 static hipError_t launch_slab(const UpdateArgs& a, hipStream_t s) {
   const int64_t blocks = a.batch * a.nheads * a.slabs_per_head;
-  hipLaunchKernelGGL((k_update_slab<F, R, NT, CPT, N128>), dim3(static_cast<unsigned>(blocks)),
+  hipLaunchKernelGGL((k_update_slab<F, R, NT, CPT, LR>), dim3(static_cast<unsigned>(blocks)),
                      dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
+// The instances for rows of a.const_lanes lanes, of the configurations that have them.
+template <int F, int R, int NT, int CPT>
+static hipError_t launch_slab_lanes(const UpdateArgs& a, hipStream_t s) {
+  if constexpr (Traits<F>::scaled) {
+    if (a.const_lanes == 4) return launch_slab<F, R, NT, CPT, 4>(a, s);
+    if (a.const_lanes == 8) return launch_slab<F, R, NT, CPT, 8>(a, s);
+    if (a.const_lanes == 16) return launch_slab<F, R, NT, CPT, 16>(a, s);
+  } else {
+    if (a.const_lanes != 0) return launch_slab<F, R, NT, CPT, 128 / Traits<F>::V>(a, s);
+  }
+  return launch_slab<F, R, NT, CPT>(a, s);
+}
+
 template <int F, int R>
 static hipError_t launch_slab_cfg(const UpdateArgs& a, int cfg, hipStream_t s) {
-  if (a.n128) {  // the configurations the dispatch picks for 128-entry rows
-    if constexpr (Traits<F>::scaled) {
-      if (cfg == kSlab128x4) return launch_slab<F, R, 128, 4, true>(a, s);
-      if (cfg == kSlab256x2) return launch_slab<F, R, 256, 2, true>(a, s);
-    } else {
-      if (cfg == kSlab512x2) return launch_slab<F, R, 512, 2, true>(a, s);
+  if (cfg == kSlab256x1) return launch_slab<F, R, 256, 1>(a, s);
+  if constexpr (!Traits<F>::scaled) {
+    if (cfg == kSlab256x2) return launch_slab<F, R, 256, 2>(a, s);
+    if (cfg == kSlab512x2) return launch_slab_lanes<F, R, 512, 2>(a, s);
+  } else {
+    if constexpr (F != kE4M3) {
+      if (cfg == kSlab256x2) return launch_slab_lanes<F, R, 256, 2>(a, s);
+    }
+    switch (cfg) {  // four chunks per thread: one scale per head, and E4M3 blocks
+      case kSlab64x4: return launch_slab<F, R, 64, 4>(a, s);
+      case kSlab128x4: return launch_slab_lanes<F, R, 128, 4>(a, s);
+      case kSlab256x4: return launch_slab<F, R, 256, 4>(a, s);
+      case kSlab512x4: return launch_slab<F, R, 512, 4>(a, s);
+      case kSlab1024x4: return launch_slab<F, R, 1024, 4>(a, s);
+      case kSlab1024x8: return launch_slab<F, R, 1024, 8>(a, s);
+      default: break;
     }
   }
-  switch (cfg) {
-    case kSlab64x4: return launch_slab<F, R, 64, 4>(a, s);
-    case kSlab128x4: return launch_slab<F, R, 128, 4>(a, s);
-    case kSlab256x1: return launch_slab<F, R, 256, 1>(a, s);
-    case kSlab256x2: return launch_slab<F, R, 256, 2>(a, s);
-    case kSlab256x4: return launch_slab<F, R, 256, 4>(a, s);
-    case kSlab512x2: return launch_slab<F, R, 512, 2>(a, s);
-    case kSlab512x4: return launch_slab<F, R, 512, 4>(a, s);
-    case kSlab1024x4: return launch_slab<F, R, 1024, 4>(a, s);
-    case kSlab1024x8: return launch_slab<F, R, 1024, 8>(a, s);
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 template <int F, int R>

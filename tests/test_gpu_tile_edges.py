@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2609_39185_amd import workloads as wl
 
-from ._parity import DEV, Bar, say, y_magnitude
+from ._parity import DEV, Bar, check_step, say, y_magnitude
 from .test_gpu_checkpoint import _codes_of
 
 pytestmark = pytest.mark.gpu
@@ -163,3 +163,17 @@ def test_requantize_spans(ssmq, fmt, rule, group, n):
     assert np.array_equal(got.ravel(), np.asarray(want).ravel())
     if sc:
         assert np.array_equal(sc.check("scale").numpy(), wsc)
+
+
+# head slabs whose lanes per row are constant (rows of 4, 8 and 16 lanes; a group per row or
+# one per head) and the general ones beside them (other rows, groups of part of a row or of two)
+@pytest.mark.parametrize("headdim,dstate", [(128, 64), (64, 128), (32, 256), (64, 256), (128, 128), (256, 32)])
+@pytest.mark.parametrize("fmt,group,rule", [
+    ("int8", "row", "weyl"), ("int4", "row", "rtn"), ("e4m3", "row", "sr"), ("e4m3", 0, "weyl"),
+    ("int8", 0, "philox"), ("int4", 16, "weyl"), ("int8", "rows", "rtn"), ("fp32", 0, "weyl"),
+    ("fp16", 0, "sr")])
+def test_slab_rows(ssmq, headdim, dstate, fmt, group, rule):
+    group = {"row": dstate, "rows": 2 * dstate}.get(group, group)
+    more = {"scale_group": group} if fmt in ("e4m3", "int8", "int4") else {}
+    check_step(fmt, rule, "mamba2", 2, 3, headdim, dstate, 1, seed=headdim + dstate,
+               what=f"slab {headdim}x{dstate} group {group}", dither_block=16, step=4, layer=1, **more)
