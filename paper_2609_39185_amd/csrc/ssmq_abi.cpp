@@ -227,7 +227,7 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
     }
   }
   if (cfg >= 0)
-    a.const_lanes = (scaled ? a.lanes_per_group == 0 || a.lanes_per_group == a.lanes_per_row
+    a.const_lanes = (scaled ? a.lanes_per_group <= 1 || a.lanes_per_group == a.lanes_per_row
                             : d.dstate == 128)
                         ? a.lanes_per_row : 0;
   if (cfg >= 0) {  // threshold base advance per pass of NT chunks

@@ -64,20 +64,22 @@ __device__ inline float silu(float v) { return v / (1.0f + expf(-v)); }
 // 128-register line; they are held to it (four waves per SIMD) instead of
 // dropping to three waves.
 //
-// LR > 0: a row is LR lanes and a scale group one row or the whole head, so the lanes
-// per row and per group are compile-time constants: the reductions lose their runtime
+// LR > 0: a row is LR lanes and a scale group LG lanes (one row, or one lane) or the whole
+// head, so the lanes per row and per group are compile-time constants: the reductions lose their runtime
 // width tests. 44M entries, one group per row: 64x256 heads INT8 Weyl 25.6 -> 22.6 us, RTN
 // 22.1 -> 18.3 us; 32x256 INT4 RTN 18.0 -> 14.3 us; 128x64 INT8 Weyl 23.9 -> 21.7 us.
+// A group per lane (blocks of 16), 44M entries: INT8 Weyl 24.9 -> 23.0 us, RTN 22.8 -> 20.5 us, INT4 RTN
+// 20.4 -> 17.0 us, E4M3 RTN 22.5 -> 21.5 us.
 constexpr int log2c(int v) { return v <= 1 ? 0 : 1 + log2c(v / 2); }
 
-template <int F, int R, int NT, int CPT, int LR = 0>
+template <int F, int R, int NT, int CPT, int LR = 0, int LG = LR>
 __global__ __launch_bounds__(NT, (Traits<F>::scaled && CPT == 4 && NT <= 128) ? 4 : 1)
 void k_update_slab(UpdateArgs a) {
   constexpr int V = Traits<F>::V;
   constexpr int NW = NT / 64;
   const int lanes_per_row = LR ? LR : a.lanes_per_row;
   const int lr_shift = LR ? log2c(LR) : a.lr_shift;
-  const int lanes_per_group = LR ? LR : a.lanes_per_group;  // when not the whole head
+  const int lanes_per_group = LR ? LG : a.lanes_per_group;  // when not the whole head
   const int t = threadIdx.x;
   const uint32_t blk = blockIdx.x;
   const uint32_t tile32 = a.div_slabs.div(blk);  // b * nheads + h
@@ -1031,10 +1033,10 @@ __global__ __launch_bounds__(256) void k_conv1d_update(ConvArgs a) {
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-template <int F, int R, int NT, int CPT, int LR = 0>
+template <int F, int R, int NT, int CPT, int LR = 0, int LG = LR>
 static hipError_t launch_slab(const UpdateArgs& a, hipStream_t s) {
   const int64_t blocks = a.batch * a.nheads * a.slabs_per_head;
-  hipLaunchKernelGGL((k_update_slab<F, R, NT, CPT, LR>), dim3(static_cast<unsigned>(blocks)),
+  hipLaunchKernelGGL((k_update_slab<F, R, NT, CPT, LR, LG>), dim3(static_cast<unsigned>(blocks)),
                      dim3(NT), 0, s, a);
   return hipGetLastError();
 }
@@ -1042,6 +1044,14 @@ static hipError_t launch_slab(const UpdateArgs& a, hipStream_t s) {
 // The instances for rows of a.const_lanes lanes, of the configurations that have them.
 template <int F, int R, int NT, int CPT>
 static hipError_t launch_slab_lanes(const UpdateArgs& a, hipStream_t s) {
+  if constexpr (F == kE4M3 || (is_int_fmt<F> && CPT == 2)) {  // the block configurations
+    if (a.lanes_per_group == 1) {
+      if (a.const_lanes == 4) return launch_slab<F, R, NT, CPT, 4, 1>(a, s);
+      if (a.const_lanes == 8) return launch_slab<F, R, NT, CPT, 8, 1>(a, s);
+      if (a.const_lanes == 16) return launch_slab<F, R, NT, CPT, 16, 1>(a, s);
+      return launch_slab<F, R, NT, CPT>(a, s);
+    }
+  }
   if constexpr (Traits<F>::scaled) {
     if (a.const_lanes == 4) return launch_slab<F, R, NT, CPT, 4>(a, s);
     if (a.const_lanes == 8) return launch_slab<F, R, NT, CPT, 8>(a, s);

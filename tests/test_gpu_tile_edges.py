@@ -170,7 +170,7 @@ def test_requantize_spans(ssmq, fmt, rule, group, n):
 @pytest.mark.parametrize("headdim,dstate", [(128, 64), (64, 128), (32, 256), (64, 256), (128, 128), (256, 32)])
 @pytest.mark.parametrize("fmt,group,rule", [
     ("int8", "row", "weyl"), ("int4", "row", "rtn"), ("e4m3", "row", "sr"), ("e4m3", 0, "weyl"),
-    ("int8", 0, "philox"), ("int4", 16, "weyl"), ("int8", "rows", "rtn"), ("fp32", 0, "weyl"),
+    ("int8", 0, "philox"), ("int4", 16, "weyl"), ("int8", 16, "sr"), ("e4m3", 16, "rtn"), ("int8", "rows", "rtn"), ("fp32", 0, "weyl"),
     ("fp16", 0, "sr")])
 def test_slab_rows(ssmq, headdim, dstate, fmt, group, rule):
     group = {"row": dstate, "rows": 2 * dstate}.get(group, group)
