@@ -257,14 +257,22 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
     a.lanes_per_group = scaled ? static_cast<int32_t>(group / 16) : 1;
     if (d.a_per_state && d.headdim == 1 && d.dstate == ssmq::kChannelN && d.ngroups == 1 && !fp32_state) {
       const int64_t tiles = (static_cast<int64_t>(d.nheads) * a.lanes_per_row + 255) / 256;
-      // As many sequences per workgroup as leave 2048 workgroups, two rounds of the 1024
-      // that fit the chip (INT8, 5120 channels, batch 225: 1, 2, 3, 5 and 7 sequences
-      // 24.2, 22.3, 21.9, 23.9 and 26.2 us).
-      int64_t per = tiles * d.batch / 2048;
-      per = per < 1 ? 1 : per > ssmq::kChannelBatch ? ssmq::kChannelBatch : per;
-      if ((d.batch + per - 1) / per <= 65535) {
+      // The batch is split evenly over as many workgroups as run at once (four per CU, five
+      // for the 16-bit formats, by registers), or twice, three times that many where one
+      // round would give a workgroup more than kChannelBatch sequences. INT8, Weyl, against
+      // at most two sequences each: 60 x 5120 channels 9.3 -> 8.7 us, 300 x 1536 12.5 -> 11.8 us;
+      // hash SR, 100 x 4096 14.1 -> 12.2 us; 1600 workgroups of eight (INT4, 400 x 8192) 58.2 us,
+      // 2048 of six 53.5 us.
+      const int64_t fit = scaled ? 1024 : 1280;
+      const int64_t turns = (tiles * d.batch + fit * ssmq::kChannelBatch - 1) / (fit * ssmq::kChannelBatch);
+      const int64_t least = (d.batch + ssmq::kChannelBatch - 1) / ssmq::kChannelBatch;
+      int64_t parts = turns * fit / tiles;
+      if (parts < least) parts = least;
+      if (parts > d.batch) parts = d.batch;
+      if (parts <= 65535) {
         cfg = ssmq::kChannelKernel;
-        a.batch_per_wg = static_cast<int32_t>(per);
+        a.batch_per_wg = static_cast<int32_t>(d.batch / parts);
+        a.batch_rem = static_cast<int32_t>(d.batch % parts);
       }
     }
     a.div_headdim = ssmq::make_fastdiv(static_cast<uint32_t>(d.headdim));

@@ -529,8 +529,9 @@ __global__ __launch_bounds__(256, 4) void k_update_channels(UpdateArgs a) {
   const int tile = static_cast<int>(blockIdx.x) * (256 / LR) + t / LR;
   const bool live = tile < a.nheads;  // whole rows (and groups) are live or dead together
   const int ch = live ? tile : 0;
-  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * a.batch_per_wg;
-  const int nb = static_cast<int>(min(static_cast<int64_t>(a.batch_per_wg), a.batch - b0));
+  const int part = static_cast<int>(blockIdx.y);  // the first batch_rem parts take one more
+  const int64_t b0 = static_cast<int64_t>(part) * a.batch_per_wg + min(part, a.batch_rem);
+  const int nb = a.batch_per_wg + (part < a.batch_rem ? 1 : 0);
 
   __shared__ float4 sBC[kChannelBatch * 2 * N / 4];  // per sequence: B, then C
   __shared__ double sExp[kExpTable];
@@ -1108,7 +1109,7 @@ static hipError_t launch_rows(const UpdateArgs& a, bool a_per_state, hipStream_t
 template <int F, int R>
 static hipError_t launch_channels(const UpdateArgs& a, hipStream_t s) {
   const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.nheads) * kChannelN / Traits<F>::V + 255) / 256);
-  const unsigned parts = static_cast<unsigned>((a.batch + a.batch_per_wg - 1) / a.batch_per_wg);
+  const unsigned parts = static_cast<unsigned>((a.batch - a.batch_rem) / a.batch_per_wg);
   hipLaunchKernelGGL((k_update_channels<F, R>), dim3(tiles, parts), dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -71,7 +71,8 @@ struct UpdateArgs {
   int32_t dstate_shift;     // log2(dstate)
   int32_t group_shift;      // E4M3: log2(entries per scale) when that is a power of two
   int32_t lanes_per_group;  // E4M3: group / 16 lanes; 0 = one scale per head slab
-  int32_t batch_per_wg;     // channel kernel: sequences per workgroup
+  int32_t batch_per_wg;     // channel kernel: sequences per workgroup ...
+  int32_t batch_rem;        // ... and one more in the first batch_rem parts
   int32_t slabs_per_head;   // slab kernels: workgroups per (batch, head) tile
   int64_t head_size;        // headdim * dstate
   int64_t n_chunks;         // total entries / V

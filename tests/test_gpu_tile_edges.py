@@ -177,3 +177,27 @@ def test_slab_rows(ssmq, headdim, dstate, fmt, group, rule):
     more = {"scale_group": group} if fmt in ("e4m3", "int8", "int4") else {}
     check_step(fmt, rule, "mamba2", 2, 3, headdim, dstate, 1, seed=headdim + dstate,
                what=f"slab {headdim}x{dstate} group {group}", dither_block=16, step=4, layer=1, **more)
+
+
+# batches that split unevenly over the workgroups of the Mamba-1 kernel, up to the most
+# sequences that one takes and one sequence past a round of workgroups: every sequence has the
+# bits of a call of its own
+@pytest.mark.parametrize("fmt,group,b,h", [("int8", 16, 100, 4096), ("int4", 16, 510, 4096),
+                                           ("e4m3", 16, 513, 4096), ("fp16", 0, 319, 4096)])
+def test_channel_parts(ssmq, fmt, group, b, h):
+    say(f"case channel parts {fmt} b{b} h{h}")
+    A, D = wl.layer_params("mamba1", h, 16, 390, device=DEV)
+    x, dt, B, C = wl.step_inputs(b, h, 1, 16, 1, 391, device=DEV)
+    codes, scale = wl.initial_state(fmt, b, h, 1, 16, 392, group=group, device=DEV)
+    q = {"rule": "weyl", "fmt": fmt, "scale_group": group, "step": 9, "layer": 2}
+    st, y = codes.clone(), torch.full((b, h, 1), 77.0, device=DEV)
+    sc = scale.clone() if group else None
+    ssmq.state_update(st, sc, x, dt, A, B, C, D, y, **q)
+    for i in sorted({0, 1, 2, 7, 8, b // 2, b // 3, b - 9, b - 8, b - 2, b - 1}):
+        s = slice(i, i + 1)
+        one, y1 = codes[s].clone(), torch.zeros((1, h, 1), device=DEV)
+        sc1 = scale.view(b, h)[i].clone() if group else None
+        ssmq.state_update(one, sc1, x[s].clone(), dt[s].clone(), A, B[s].clone(), C[s].clone(), D, y1,
+                          entry_base=i * h * 16, **q)
+        assert torch.equal(one, st[s]) and torch.equal(y1, y[s]), i
+        assert not group or torch.equal(sc1, sc.view(b, h)[i]), i
