@@ -911,7 +911,7 @@ def _grid(row) -> int:
 def _variant_of(kernel_name: str):
     import re
 
-    m = re.search(r"k_update_(?:slab|rows)<(\d+), (\d+)", kernel_name)
+    m = re.search(r"k_update_(?:slab|rows|channels)<(\d+), (\d+)", kernel_name)
     if not m:
         return None
     f = {v: k for k, v in _FMT_CODE.items()}[int(m.group(1))]
@@ -1052,7 +1052,7 @@ def summarize_replay_trace(trace_dir: str, name: str) -> int:
              "| kernel | format:rule | calls | full-size launch us | trace GB/s |",
              "|---|---|---|---|---|"]
     for r in sorted(stats, key=lambda r: r["Name"]):
-        km = re.search(r"k_replay<(\d+), (\d+)>", r["Name"])
+        km = re.search(r"k_replay<(\d+), (\d+)", r["Name"])
         if not km:
             continue
         key = f"{fmts[int(km.group(1))]}:{rules[int(km.group(2))]}"
@@ -1078,7 +1078,7 @@ def summarize_entry_points_trace(trace_dir: str) -> int:
              f"    {PROFILE_COMMANDS['entry_trace']}",
              f"    {PROFILE_COMMANDS['entry_trace_summary']}", "",
              "Template arguments: format code (0 fp16, 1 bf16, 2 E4M3, 4 INT8, 5 INT4), rule code "
-             "(0 RTN, 1 hash SR, 2 Weyl, 3 Philox), and for the per-group kernel the chunks per thread.", "",
+             "(0 RTN, 1 hash SR, 2 Weyl, 3 Philox), and for the per-group kernel the threads and the chunks per thread.", "",
              "| kernel | calls | avg us | min us | max us |", "|---|---|---|---|---|"]
     for r in sorted(stats, key=lambda r: r["Name"]):
         if not re.search(r"k_requant|k_dither_fill", r["Name"]):
