@@ -26,6 +26,8 @@ def build(verbose: bool = False) -> str:
            "-Wl,-rpath,$ORIGIN/../paper_2609_39185_amd:$ORIGIN/../oracle:" + os.path.join(ROCM, "lib")]
     if verbose:
         print(" ".join(cmd), flush=True)
+    if os.path.exists(BINARY):
+        os.remove(BINARY)  # a failed compile leaves no older program to be run in its place
     subprocess.run(cmd, check=True)
     os.replace(tmp, BINARY)
     build_scale_check(verbose)
@@ -43,6 +45,8 @@ def build_scale_check(verbose: bool = False) -> str:
            "-I", os.path.join(ROOT, "paper_2609_39185_amd", "csrc"), SCALE_SOURCE, "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
+    if os.path.exists(SCALE_BINARY):
+        os.remove(SCALE_BINARY)  # a failed compile leaves no older program to be run in its place
     subprocess.run(cmd, check=True)
     os.replace(tmp, SCALE_BINARY)
     return SCALE_BINARY

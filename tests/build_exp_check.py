@@ -19,6 +19,8 @@ def build(verbose: bool = False) -> str:
     cmd = [hip_build.hipcc(), *flags, "-I", hip_build.CSRC, SOURCE, "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
+    if os.path.exists(BINARY):
+        os.remove(BINARY)  # a failed compile leaves no older program to be run in its place
     subprocess.run(cmd, check=True)
     os.replace(tmp, BINARY)
     return BINARY
