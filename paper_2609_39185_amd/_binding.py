@@ -8,12 +8,14 @@ The per-token calls (state_update, conv1d_update, requantize) go through the
 _native module first, which reads plain tensors and integers in C++: 1536 Mamba-1
 channels, conv1d_update and state_update, 17.0 -> 8.1 us for both. What it leaves
 (returns None for: other types, shapes that do not fit, wrapped tensors) takes the
-ctypes path, which accepts or rejects it.
+ctypes path, which accepts or rejects it; where the module cannot be loaded, every call does.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import torch  # imported first so the HIP runtime is the one torch already loaded
 
@@ -58,17 +60,34 @@ _lib = None
 _native = None
 
 
+class _CtypesOnly:
+    """In place of the _native module where that cannot be loaded: leaves every call."""
+    state_update = conv1d_update = requantize = staticmethod(lambda *args: None)
+
+
+def _import_native():
+    """The _native module; ImportError if it is missing or was built for another torch or Python."""
+    from . import _native as module
+    need = f"torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+    built_for = getattr(module, "BUILT_FOR", "another version")
+    if built_for != need:
+        raise ImportError(f"built for {built_for}, not {need}")
+    return module
+
+
 def _load_native():
-    """The _native module, loaded once; raises if it has not been built."""
+    """The _native module, or, with a warning, the stand-in that leaves its calls to ctypes.
+    Chosen once per process."""
     global _native
     if _native is None:
         library()  # its symbols come from the library that ctypes loads
         try:
-            from . import _native as module
+            _native = _import_native()
         except ImportError as e:
-            raise RuntimeError(f"the _native module cannot be loaded ({e}): build it with "
-                               "paper_2609_39185_amd.build.build()") from e
-        _native = module
+            warnings.warn(f"the _native module cannot be loaded ({e}): calls go through ctypes, which takes "
+                          "longer on the host; paper_2609_39185_amd.build.build() builds it", RuntimeWarning,
+                          stacklevel=3)
+            _native = _CtypesOnly
     return _native
 
 

@@ -169,4 +169,17 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_native", "Per-token calls of lib
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&kModule); }
+#define SSMQ_STR_(v) #v
+#define SSMQ_STR(v) SSMQ_STR_(v)
+
+PyMODINIT_FUNC PyInit__native() {
+  PyObject* const m = PyModule_Create(&kModule);
+  // What the importer compares: torch's tensor layout and CPython's are compiled in.
+  if (m && PyModule_AddStringConstant(m, "BUILT_FOR",
+                                      "torch " SSMQ_TORCH_VERSION ", Python " SSMQ_STR(PY_MAJOR_VERSION) "." SSMQ_STR(
+                                          PY_MINOR_VERSION)) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -32,3 +32,25 @@ def test_build_does_not_depend_on_the_test_programs(case, tmp_path, monkeypatch)
     for name, text in (programs or {}).items():
         built = os.path.exists(tmp_path / "tests" / f"{name}.py.built")
         assert built == (text is GOOD), name
+
+
+@pytest.mark.parametrize("how", ["no compiler", "compile error"])
+def test_library_is_usable_without_the_module(how, tmp_path, monkeypatch):
+    """Where the marshalling module does not compile, build() keeps the library and leaves
+    no older module beside it."""
+    import subprocess
+
+    def stand_in(cmd, **kw):
+        if cmd[0] == "g++":
+            if how == "no compiler":
+                raise FileNotFoundError("g++")
+            raise subprocess.CalledProcessError(1, cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+
+    library, native = str(tmp_path / "libssmq.so"), str(tmp_path / "_native.so")
+    open(native, "w").close()
+    monkeypatch.setattr(hip_build, "LIBRARY", library)
+    monkeypatch.setattr(hip_build, "NATIVE", native)
+    monkeypatch.setattr(hip_build.subprocess, "run", stand_in)
+    assert hip_build.build() == library
+    assert os.path.exists(library) and not os.path.exists(native)

@@ -132,3 +132,51 @@ def test_other_calls_same_as_ctypes(binding, monkeypatch, case):
     print(f"case native {case}", flush=True)
     got, want = _both(binding, monkeypatch, make)
     assert got == want
+
+
+@pytest.mark.parametrize("why", ["missing", "other torch", "no version"])
+def test_ctypes_takes_over_without_the_module(binding, monkeypatch, why):
+    """Where the module cannot be loaded, or was built for another torch, calls reach the
+    ctypes path (here its refusal of CPU tensors), with one warning per process."""
+    import sys
+    import types
+
+    name = "paper_2609_39185_amd._native"
+    fake = types.ModuleType(name)  # an older module: taking a call would be a mistake
+    fake.state_update = fake.conv1d_update = fake.requantize = lambda *a: 0
+    if why == "other torch":
+        fake.BUILT_FOR = "torch 1.0, Python 3.10"
+    monkeypatch.setitem(sys.modules, name, None if why == "missing" else fake)
+    if why != "missing":
+        monkeypatch.setattr(sys.modules["paper_2609_39185_amd"], "_native", fake, raising=False)
+    else:
+        monkeypatch.delattr(sys.modules["paper_2609_39185_amd"], "_native", raising=False)
+    monkeypatch.setattr(binding, "_native", None)
+    t = torch.zeros(1, 2, 4)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        with pytest.raises(ValueError, match="GPU memory"):
+            binding.conv1d_update(t, t[0], t[0], None, t[0])
+    import warnings
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        with pytest.raises(ValueError, match="GPU memory"):
+            binding.requantize(t, torch.zeros(8, dtype=torch.int16), None, rule="rtn", fmt="bf16")
+
+
+@pytest.mark.gpu
+def test_step_without_the_module(binding, monkeypatch):
+    """The same bits through the stand-in that serves calls where the module is missing."""
+    dev = torch.device("cuda:0")
+    codes = torch.linspace(-2, 2, 4 * N, device=dev)
+
+    def make():
+        out = torch.zeros(4 * N, dtype=torch.int16, device=dev)
+        binding.requantize(codes, out, None, rule="weyl", fmt="bf16", step=3)
+        torch.cuda.synchronize()
+        return out.cpu().numpy().tobytes()
+
+    assert binding._load_native() is not binding._CtypesOnly, "run __graft_entry__.build()"
+    want = make()
+    monkeypatch.setattr(binding, "_native", binding._CtypesOnly)
+    print("case native stand-in", flush=True)
+    assert make() == want
