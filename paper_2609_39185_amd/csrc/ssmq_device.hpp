@@ -694,7 +694,7 @@ __device__ inline float recip_scale(float s) {
 // argument the results are those of (float)exp((double)z) (checked on the device).
 // Two forms, both without a branch but for |z| > 700, where the double's exponent
 // would wrap (the result is 0 or infinity there):
-//   exp_value         k = rint(z log2 e), r = z - k ln 2 (ln 2 in two doubles), exp(r)
+//   exp_values        k = rint(z log2 e), r = z - k ln 2 (ln 2 in two doubles), exp(r)
 //                     on |r| <= ln 2 / 2 by a degree-11 minimax polynomial (Remez
 //                     exchange, relative error 2^-53.7): 17 double operations.
 //   exp_values_table  k = rint(z 256 / ln 2), 2^(k mod 256 / 256) from a table in LDS
@@ -729,35 +729,40 @@ __device__ inline void exp_out_of_range(const float (&z)[N], float (&out)[N]) {
     }
   }
 }
-// p = fma(p, r, c), c in a scalar register pair: left to itself the compiler takes the
-// two-operand form, which overwrites its addend, and copies c into vector registers
-// for every term.
-__device__ inline double fma_s(double p, double r, double c) {
-  double d;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(r), "s"(c));
-  return d;
-}
-__device__ inline float exp_value(float zf) {
-  const float za[1] = {zf};
+__device__ inline float exp_in_range(float zf) {
   const double z = static_cast<double>(zf);
   const double t = __builtin_fma(z, 0x1.71547652b82fep+0, 0x1.8p52);  // k in the low bits
   const uint32_t k = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, t));
   const double kd = t - 0x1.8p52;
   double r = __builtin_fma(kd, -0x1.62e42fefa39efp-1, z);
   r = __builtin_fma(kd, -0x1.abc9e3b39803fp-56, r);
-  double p = fma_s(r, 0x1.8ad0f40784e9dp-26, 0x1.28a2c68333593p-22);
-  p = fma_s(p, r, 0x1.71f6152e4b934p-19);
-  p = fma_s(p, r, 0x1.a019a66a00698p-16);
-  p = fma_s(p, r, 0x1.a019f62058ba4p-13);
-  p = fma_s(p, r, 0x1.6c16c17f41b14p-10);
-  p = fma_s(p, r, 0x1.111111137ba72p-7);
-  p = fma_s(p, r, 0x1.55555555520c1p-5);
-  p = fma_s(p, r, 0x1.555555555481ap-3);
-  p = fma_s(p, r, 0x1.0000000000005p-1);
-  p = fma_s(p, r, 0x1.0000000000003p+0);
+  double p = __builtin_fma(r, 0x1.8ad0f40784e9dp-26, 0x1.28a2c68333593p-22);
+  p = __builtin_fma(p, r, 0x1.71f6152e4b934p-19);
+  p = __builtin_fma(p, r, 0x1.a019a66a00698p-16);
+  p = __builtin_fma(p, r, 0x1.a019f62058ba4p-13);
+  p = __builtin_fma(p, r, 0x1.6c16c17f41b14p-10);
+  p = __builtin_fma(p, r, 0x1.111111137ba72p-7);
+  p = __builtin_fma(p, r, 0x1.55555555520c1p-5);
+  p = __builtin_fma(p, r, 0x1.555555555481ap-3);
+  p = __builtin_fma(p, r, 0x1.0000000000005p-1);
+  p = __builtin_fma(p, r, 0x1.0000000000003p+0);
   p = __builtin_fma(p, r, 1.0);
-  float out[1] = {static_cast<float>(add_exponent<20>(p, k))};
-  exp_out_of_range<1>(za, out);
+  return static_cast<float>(add_exponent<20>(p, k));
+}
+// N of them in one stretch of code, so that their chains overlap, with one test of the
+// range: a branch for each left every chain of 17 operations to itself. Row kernel, E4M3 RTN,
+// 2048 channels of 64 states, from a graph: one sequence 4.01 -> 3.45 us (with the library's
+// exp 3.45), 64 sequences 11.9 -> 10.3 us (11.3).
+template <int N>
+__device__ inline void exp_values(const float (&z)[N], float (&out)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) out[i] = exp_in_range(z[i]);
+  exp_out_of_range<N>(z, out);
+}
+__device__ inline float exp_value(float zf) {
+  const float z[1] = {zf};
+  float out[1];
+  exp_values<1>(z, out);
   return out[0];
 }
 
@@ -821,6 +826,14 @@ __device__ const uint64_t kExpTableBits[kExpTable] = {
 // Copies the table to LDS (a barrier of the caller's has to follow).
 __device__ inline void stage_exp_table(double* tab, int t, int threads) {
   for (int i = t; i < kExpTable; i += threads) tab[i] = __builtin_bit_cast(double, kExpTableBits[i]);
+}
+// p = fma(p, r, c), c in a scalar register pair: left to itself the compiler takes the
+// two-operand form, which overwrites its addend, and copies c into vector registers
+// for every term.
+__device__ inline double fma_s(double p, double r, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(r), "s"(c));
+  return d;
 }
 template <int N>
 __device__ inline void exp_values_table(const double* tab, const float (&z)[N], float (&out)[N]) {

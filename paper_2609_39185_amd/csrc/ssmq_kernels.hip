@@ -42,6 +42,13 @@ __device__ inline void load_floats(const float* p, float (&out)[V]) {
 
 // dA = fl32(exp(fl32(dt A))), correctly rounded.
 __device__ inline float decay(float dtv, float a) { return exp_value(dtv * a); }
+template <int N>
+__device__ inline void decays(float dtv, const float (&a)[N], float (&dA)[N]) {
+  float z[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) z[k] = dtv * a[k];
+  exp_values<N>(z, dA);
+}
 
 // The step size the update uses: dt, plus dt_bias[head] when given, through
 // softplus(v) = log(1 + e^v) (double, one rounding; v itself above 20) when asked.
@@ -459,8 +466,7 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
   if constexpr (A_PER_STATE) {
     float Av[V];
     load_floats<V>(a.A + static_cast<int64_t>(hh) * a.dstate + n0, Av);
-#pragma unroll
-    for (int k = 0; k < V; ++k) dA[k] = decay(dtv, Av[k]);
+    decays<V>(dtv, Av, dA);
   } else {
     const float d = decay(dtv, a.A[hh]);
 #pragma unroll

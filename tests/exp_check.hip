@@ -1,6 +1,7 @@
 // Exhaustive device check of the decay's exponential (test infrastructure): for every
-// fp32 bit pattern z, exp_value and exp_values_table must equal the double exp rounded once, (float)exp((double)z) (NaN for NaN). Prints the number of values
-// checked and of mismatches.
+// fp32 bit pattern z, exp_value, exp_values (z among ordinary neighbours) and
+// exp_values_table must equal the double exp rounded once, (float)exp((double)z) (NaN for
+// NaN). Prints the number of values checked and of mismatches.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -25,6 +26,8 @@ __global__ __launch_bounds__(256) void k_check_exp(unsigned long long* bad, unsi
     float e4[4];
     exp_values_table<4>(tab, four, e4);
     b += !same(exp_value(z), z) || !same(e4[1], z) || !same(e4[0], four[0]) || !same(e4[3], four[3]);
+    exp_values<4>(four, e4);
+    b += !same(e4[1], z) || !same(e4[0], four[0]) || !same(e4[2], four[2]) || !same(e4[3], four[3]);
     ++n;
   }
   atomicAdd(bad, b);
