@@ -255,21 +255,26 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
       return fail(SSMQ_EUNSUPPORTED, "state too large for one launch");
     cfg = ssmq::kRowKernel;
     a.lanes_per_group = scaled ? static_cast<int32_t>(group / 16) : 1;
-    if (d.a_per_state && d.headdim == 1 && d.dstate == ssmq::kChannelN && d.ngroups == 1 && !fp32_state) {
+    // The channel kernel's set-up (the exp table, B, C and step sizes staged, a barrier) pays from
+    // about a million chunks on and where a workgroup takes several sequences. From a graph, Weyl,
+    // row kernel / channel kernel: INT8 1 x 1536 channels 3.54 / 3.85 us, 64 x 5120 7.7 / 8.5,
+    // 192 x 5120 18.1 / 19.0, 225 x 5120 22.5 / 21.4, 400 x 8192 59.1 / 52.6; bf16 (two chunks per
+    // channel) 1 x 5120 2.91 / 3.21, 64 x 5120 7.9 / 8.0, 100 x 5120 10.7 / 10.1, 225 x 5120
+    // 23.2 / 22.0. fp32 (four chunks) takes the row kernel at every size: 16 x 5120 3.84 / 4.20,
+    // 225 x 5120 30.9 / 32.4, 400 x 8192 84.7 / 88.0 us.
+    if (d.a_per_state && d.headdim == 1 && d.dstate == ssmq::kChannelN && d.ngroups == 1 && !fp32_state &&
+        q->format != SSMQ_FP32 && a.n_chunks >= ssmq::kChannelChunks) {
       const int64_t tiles = (static_cast<int64_t>(d.nheads) * a.lanes_per_row + 255) / 256;
       // The batch is split evenly over as many workgroups as run at once (four per CU, five
       // for the 16-bit formats, by registers), or twice, three times that many where one
-      // round would give a workgroup more than kChannelBatch sequences. INT8, Weyl, against
-      // at most two sequences each: 60 x 5120 channels 9.3 -> 8.7 us, 300 x 1536 12.5 -> 11.8 us;
-      // hash SR, 100 x 4096 14.1 -> 12.2 us; 1600 workgroups of eight (INT4, 400 x 8192) 58.2 us,
-      // 2048 of six 53.5 us.
+      // round would give a workgroup more than kChannelBatch sequences: INT4, 400 x 8192
+      // channels, 1600 workgroups of eight sequences 58.2 us, 2048 of six 53.5 us.
       const int64_t fit = scaled ? 1024 : 1280;
       const int64_t turns = (tiles * d.batch + fit * ssmq::kChannelBatch - 1) / (fit * ssmq::kChannelBatch);
       const int64_t least = (d.batch + ssmq::kChannelBatch - 1) / ssmq::kChannelBatch;
       int64_t parts = turns * fit / tiles;
       if (parts < least) parts = least;
-      if (parts > d.batch) parts = d.batch;
-      if (parts <= 65535) {
+      if (parts <= 65535 && 2 * parts <= d.batch) {
         cfg = ssmq::kChannelKernel;
         a.batch_per_wg = static_cast<int32_t>(d.batch / parts);
         a.batch_rem = static_cast<int32_t>(d.batch % parts);

@@ -7,9 +7,9 @@
 //                  threshold -> round -> store, in registers, so the state
 //                  crosses HBM once each way (Section 2 eq. (rec) and eq.
 //                  (dither); Appendix B "Runners", "Formats", "Dithers").
-//   k_update_channels  the same step for Mamba-1 layers (heads of one row of 16
-//                  entries, A per (channel, n)): a workgroup takes a tile of channels through
-//                  several sequences.
+//   k_update_channels  the same step for large batches of Mamba-1 layers (heads of one
+//                  row of 16 entries, A per (channel, n)): a workgroup takes a tile of
+//                  channels through several sequences.
 //   k_update_rows  the same step for any other row layout (Mamba-2 heads smaller
 //                  than a slab, A per (head, n) with other rows or several B/C groups), and the
 //                  checkpoint write on an fp32 state.
@@ -523,13 +523,13 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
 // next sequence's state and x load while the current one is computed (one chunk per
 // lane and launch reads A anew for every sequence, 4 bytes per entry against 2 of INT8
 // state, and waits for three rounds of loads one after another). 5120 channels, batch
-// 225, INT8 blocks of 16, Weyl: 26.1 -> 22.2 us against the row kernel.
-// Four waves per SIMD: at the 128 registers of that bound nothing spills.
+// 225, INT8 blocks of 16, Weyl, from a graph: row kernel 22.5 us, this one 21.4.
+// Four waves per SIMD: at the 128 registers of that bound only INT8 hash SR spills (four).
 template <int F, int R>
 __global__ __launch_bounds__(256, 4) void k_update_channels(UpdateArgs a) {
   constexpr int V = Traits<F>::V;
   const int t = threadIdx.x;
-  constexpr int N = kChannelN, LR = N / V;  // lanes per row: 1, 2 or 4; a scaled row is one group
+  constexpr int N = kChannelN, LR = N / V;  // lanes per row: 1 or 2; a scaled row is one group
   const int cc = t & (LR - 1);
   const int n0 = cc * V;
   const int tile = static_cast<int>(blockIdx.x) * (256 / LR) + t / LR;
@@ -1122,7 +1122,9 @@ static hipError_t launch_channels(const UpdateArgs& a, hipStream_t s) {
 
 template <int F, int R>
 static hipError_t launch_update_fr(const UpdateArgs& a, int cfg, bool aps, hipStream_t s) {
-  if (cfg == kChannelKernel) return launch_channels<F, R>(a, s);
+  if constexpr (F != kFP32) {
+    if (cfg == kChannelKernel) return launch_channels<F, R>(a, s);
+  }
   return cfg == kRowKernel ? launch_rows<F, R>(a, aps, s) : launch_slab_cfg<F, R>(a, cfg, s);
 }
 

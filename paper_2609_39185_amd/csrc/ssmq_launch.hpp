@@ -48,7 +48,8 @@ constexpr int kSlabThreads[] = {64, 128, 256, 256, 256, 512, 512, 1024, 1024};
 constexpr int kSlabChunks[] = {4, 4, 1, 2, 4, 2, 4, 4, 8};
 constexpr int kMaxDstate = 1024;  // 64 lanes x 16 E4M3 entries per row
 constexpr int kChannelN = 16;      // channel kernel: entries per row ...
-constexpr int kChannelBatch = 8;   // ... and the most sequences per workgroup
+constexpr int kChannelBatch = 8;   // ... the most sequences per workgroup ...
+constexpr int64_t kChannelChunks = 1000000;  // ... and the fewest chunks of a state that takes it
 
 struct UpdateArgs {
   void* state;

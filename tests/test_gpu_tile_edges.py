@@ -82,8 +82,8 @@ def _checkpoint(ssmq, fmt, group, rule, family, shape):
     bar.check()
 
 
-# Mamba-1 layers (rows of 16): a part of a channel tile, a tile and one channel more,
-# and batches whose last workgroup has fewer sequences than the others
+# Mamba-1 layers (rows of 16) of fewer than a million chunks: a part of a workgroup's rows,
+# a workgroup and some rows more, many sequences of a few channels
 @pytest.mark.parametrize("b,h", [(1, 1), (2, 129), (3, 257), (4099, 9), (6145, 3)])
 @pytest.mark.parametrize("fmt,rule,fused", [("fp16", "weyl", True), ("bf16", "sr", False), ("fp32", "rtn", False),
                                             ("e4m3", "philox", True), ("int8", "weyl", False), ("int4", "rtn", True)])
@@ -179,9 +179,9 @@ def test_slab_rows(ssmq, headdim, dstate, fmt, group, rule):
                what=f"slab {headdim}x{dstate} group {group}", dither_block=16, step=4, layer=1, **more)
 
 
-# batches that split unevenly over the workgroups of the Mamba-1 kernel, up to the most
-# sequences that one takes and one sequence past a round of workgroups: every sequence has the
-# bits of a call of its own
+# large batches of Mamba-1 channels, split unevenly over the workgroups, up to the most
+# sequences that one takes and one sequence past a round of workgroups (and, the first, a
+# batch of fewer than a million chunks): every sequence has the bits of a call of its own
 @pytest.mark.parametrize("fmt,group,b,h", [("int8", 16, 100, 4096), ("int4", 16, 510, 4096),
                                            ("e4m3", 16, 513, 4096), ("fp16", 0, 319, 4096)])
 def test_channel_parts(ssmq, fmt, group, b, h):
@@ -201,3 +201,38 @@ def test_channel_parts(ssmq, fmt, group, b, h):
                           entry_base=i * h * 16, **q)
         assert torch.equal(one, st[s]) and torch.equal(y1, y[s]), i
         assert not group or torch.equal(sc1, sc.view(b, h)[i]), i
+
+
+# The Mamba-1 kernel that takes several sequences per workgroup, from a million chunks on:
+# ragged channel tiles and uneven parts of the batch, a channel that is NaN or infinite,
+# against a call for each of some sequences (which the row kernel takes), bit for bit
+@pytest.mark.parametrize("fmt,group,rule,b,h", [
+    ("fp16", 0, "weyl", 101, 4999), ("bf16", 0, "sr", 1300, 385), ("fp16", 0, "philox", 510, 1001),
+    ("bf16", 0, "rtn", 2048, 250), ("e4m3", 16, "sr", 1999, 513), ("int8", 16, "sr", 205, 4999),
+    ("int8", 16, "weyl", 4099, 257), ("int4", 16, "rtn", 8001, 127), ("int4", 16, "philox", 1024, 999),
+    ("e4m3", 16, "weyl", 3, 340001), ("int8", 16, "rtn", 2, 500100)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_channels_same_as_rows(ssmq, fmt, group, rule, b, h, fused):
+    assert b * h * (1 if group else 2) >= 1000000  # chunks
+    say(f"case channels as rows {fmt} {rule} b{b} h{h} fused {fused}")
+    A, D = wl.layer_params("mamba1", h, 16, 490, device=DEV)
+    x, dt, B, C = wl.step_inputs(b, h, 1, 16, 1, 491, device=DEV)
+    x[0, 0], x[b // 2, h // 2], x[b - 1, h - 1] = float("inf"), float("nan"), -float("inf")
+    codes, scale = wl.initial_state(fmt, b, h, 1, 16, 492, group=group, device=DEV)
+    q = {"rule": rule, "fmt": fmt, "scale_group": group, "step": 9, "layer": 2, "seed": 4}
+    z = torch.randn((b, h, 1), device=DEV) if fused else None
+    if fused:
+        q.update(dt_softplus=True, dt_bias=torch.linspace(-3.0, 1.0, h, device=DEV))
+    st, y = Guarded(codes.cpu()), Guarded(torch.zeros(b, h, 1))
+    sc = Guarded(scale.cpu()) if group else None
+    ssmq.state_update(st.t, sc.t if sc else None, x, dt, A, B, C, D, y.t, z=z, **q)
+    got, gy, gsc = st.check("state"), y.check("y"), sc.check("scale").view(b, h) if sc else None
+    for i in sorted({0, 1, b // 3, b // 2, max(b - 8, 0), max(b - 2, 0), b - 1}):
+        s = slice(i, i + 1)
+        one, y1 = codes[s].clone(), torch.zeros((1, h, 1), device=DEV)
+        sc1 = scale.view(b, h)[i].clone() if group else None
+        ssmq.state_update(one, sc1, x[s].clone(), dt[s].clone(), A, B[s].clone(), C[s].clone(), D, y1,
+                          entry_base=i * h * 16, z=z[s].clone() if fused else None, **q)
+        assert torch.equal(one.cpu(), got[s]), i
+        assert torch.equal(y1.cpu().nan_to_num(7.0), gy[s].nan_to_num(7.0)), i
+        assert not group or torch.equal(sc1.cpu(), gsc[i]), i
