@@ -518,16 +518,20 @@ __device__ inline uint32_t pack_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uin
 // maybe_nan: a NaN may be among h. Saturation: the group's scale maps its maximum to
 // qmax, so q passes qmax only by rounding, by at most qmax 2^-22.
 //   Round to nearest needs no clamp: such a q still rounds to qmax.
-//   INT8 dithers need none either: X + U then leaves the range of the codes
+//   Dithers clamp to +-qmax before the floor (CLAMP: v_med3_f32, one instruction per
+//   entry; the bounds are lattice points, so this is the exact saturation).
+//   INT8 dithers can do without (CLAMP = false): X + U then leaves the range of the codes
 //   -127 .. 127 only if U lies within 2^9 of an end of its range, and a sum that has
 //   done so reads, as a signed word, less than -127 2^24. The chunk's smallest sum
-//   (half an instruction per entry) sends those to the exact path.
-//   INT4 dithers clamp to +-qmax before the floor (v_med3_f32, one instruction per
-//   entry; the bounds are lattice points, so this is the exact saturation).
+//   (half an instruction per entry) sends those to the exact path. It takes registers, so
+//   it is left to the kernels where it pays: blocks with two chunks per thread, and
+//   Mamba-1's. Elsewhere, 21M to 42M entries, Weyl, from a graph, without / with the clamp:
+//   64x128 heads, one scale each (two spills more) 23.0 / 21.8 us; 64x64 heads, blocks of
+//   16 (one chunk per thread, 74 / 66 registers) 13.5 / 13.1; rows of 48x128 heads 25.1 / 23.9.
 // One layer of 268M entries in blocks of 128, against a clamp everywhere: INT8 Weyl
 // 119.8 -> 118.1 us, INT8 RTN 97.7 -> 93.9 us, INT4 RTN 81.8 -> 77.6 us.
 constexpr int32_t kInt8Low = -127 * (1 << 24);
-template <int F, int R, typename TG>
+template <int F, int R, bool CLAMP, typename TG>
 __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, float r24,
                                                const TG& tg, bool maybe_nan) {
   constexpr float qmax = Traits<F>::qmax;
@@ -547,11 +551,11 @@ __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, f
       const float q24 = h[k] * r24;
       mn = fminf(mn, __builtin_fabsf(q24));
       float c24 = q24;
-      if constexpr (F == kINT4) c24 = __builtin_amdgcn_fmed3f(q24, -qmax * 0x1p24f, qmax * 0x1p24f);
+      if constexpr (CLAMP) c24 = __builtin_amdgcn_fmed3f(q24, -qmax * 0x1p24f, qmax * 0x1p24f);
       int X;  // floor
       asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(X) : "v"(c24));
       S[k] = static_cast<uint32_t>(X) + (tg(k) >> 8);
-      if constexpr (F == kINT8) low = min(low, static_cast<int32_t>(S[k]));
+      if constexpr (!CLAMP) low = min(low, static_cast<int32_t>(S[k]));
     }
     rare = rare || !(mn >= 0x1p-102f) || !(r24 < __builtin_inff()) || low < kInt8Low;
   }
@@ -579,9 +583,9 @@ __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, f
         exact = h[k] != h[k];
       } else {
         // NaN, q below the normal range (q24 then differs from q 2^24), r24 overflowed, or
-        // an INT8 sum out of the codes' range
+        // an unclamped sum out of the codes' range
         exact = !(__builtin_fabsf(h[k] * r24) >= 0x1p-102f) || !(r24 < __builtin_inff()) ||
-                (F == kINT8 && static_cast<int32_t>(S[k]) < kInt8Low);
+                (!CLAMP && static_cast<int32_t>(S[k]) < kInt8Low);
       }
       if (exact) patch_code<F>(w, k, round_code<F, R>(h[k] * r, tg(k)));
     }
@@ -591,12 +595,13 @@ __device__ inline chunk_t<F> quantize_int_chunk(const float (&h)[16], float r, f
 }
 
 // One chunk of fp32 values h -> codes, for every format: r = 1 / s of the
-// chunk's group (ignored by unscaled formats).
-template <int F, int R, typename TG>
+// chunk's group (ignored by unscaled formats). INT_CLAMP: the integer formats' dithers
+// clamp (see quantize_int_chunk).
+template <int F, int R, bool INT_CLAMP = true, typename TG>
 __device__ inline chunk_t<F> quantize_any(const float (&h)[Traits<F>::V], float r, const TG& tg,
                                          bool maybe_nan, bool clamp = true) {
   if constexpr (is_int_fmt<F>) {
-    return quantize_int_chunk<F, R>(h, r, r * 0x1p24f, tg, maybe_nan);
+    return quantize_int_chunk<F, R, INT_CLAMP>(h, r, r * 0x1p24f, tg, maybe_nan);
   } else if constexpr (F == kE4M3) {
     return quantize_e4m3_chunk<R>(h, r, tg, maybe_nan, clamp);
   } else {

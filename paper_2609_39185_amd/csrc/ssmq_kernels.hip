@@ -306,6 +306,8 @@ void k_update_slab(UpdateArgs a) {
     }
   }
 
+  // See quantize_int_chunk for what the clamp costs and saves.
+  constexpr bool kClamp = F == kINT4 || CPT == 1 || (CPT == 4 && NT <= 128);
   // Threshold bases of the chunks: one pass of NT chunks apart, a constant
   // step when the pass spans whole dither blocks. The direct form is kept
   // inside its branch by the empty asm: if-converted, its two 32-bit
@@ -325,7 +327,7 @@ void k_update_slab(UpdateArgs a) {
   for (int j = 0; j < CPT; ++j) {
     const int64_t e = e0 + static_cast<int64_t>(j) * pass;
     const uint32_t base = bases[j];
-    const chunk_t<F> out = quantize_any<F, R>(
+    const chunk_t<F> out = quantize_any<F, R, kClamp>(
         h[j], r[j], chunk_thr<R, V>(a.entry_base + static_cast<uint64_t>(e), a.thr, base, a.toff),
         bad[j], clamp);
     store_stream(hstate + chunk_bytes_at<F>(l0 + j * pass), out);
@@ -498,8 +500,8 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
     if (live && a.scale && (t & (a.lanes_per_group - 1)) == 0) a.scale[e >> a.group_shift] = s;
   }
   const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
-  const chunk_t<F> out =
-      quantize_any<F, R>(h, rs, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), bad);
+  const chunk_t<F> out = quantize_any<F, R, F == kINT4 || !A_PER_STATE>(
+      h, rs, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), bad);
   if constexpr (FP32_STATE) {
     float v[V];
     decode_chunk<F>(out, v);
@@ -524,7 +526,8 @@ __global__ __launch_bounds__(256) void k_update_rows(UpdateArgs a) {
 // lane and launch reads A anew for every sequence, 4 bytes per entry against 2 of INT8
 // state, and waits for three rounds of loads one after another). 5120 channels, batch
 // 225, INT8 blocks of 16, Weyl, from a graph: row kernel 22.5 us, this one 21.4.
-// Four waves per SIMD: at the 128 registers of that bound only INT8 hash SR spills (four).
+// Four waves per SIMD: at the 128 registers of that bound only INT8 hash SR spills (two; four
+// without its clamp).
 template <int F, int R>
 __global__ __launch_bounds__(256, 4) void k_update_channels(UpdateArgs a) {
   constexpr int V = Traits<F>::V;
@@ -631,7 +634,7 @@ __global__ __launch_bounds__(256, 4) void k_update_channels(UpdateArgs a) {
     }
     const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
     const chunk_t<F> out =
-        quantize_any<F, R>(h, rs, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), bad);
+        quantize_any<F, R, F == kINT4 || R == kSR>(h, rs, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff), bad);
     if (live) store_stream(state + chunk_bytes_at<F>(e), out);
   }
 }
