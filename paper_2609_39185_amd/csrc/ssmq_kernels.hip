@@ -651,24 +651,25 @@ __device__ inline void store_code(void* codes, int64_t k, uint32_t c) {
   else static_cast<uint8_t*>(codes)[k] = static_cast<uint8_t>(c);
 }
 
-// The fp32 entries of the 16-bit formats come through LDS in whole lines (see FpSpan):
-// bf16, 63M entries (377 MB) 64.3 -> 62.5 us.
-template <int F, int R>
+// STREAM (see kRequantStream; 16-bit formats): the fp32 entries come past the caches, through
+// LDS in whole lines (see FpSpan). bf16 Weyl, from a graph, without / with it: 63M entries of
+// one buffer 64.0 / 56.1 us, of three in turn 64.6 / 62.2; 15M of one 14.4 / 16.6.
+template <int F, int R, bool STREAM>
 __global__ __launch_bounds__(256) void k_requant(RequantArgs a) {
   constexpr int V = Traits<F>::V;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t e = q * V;
   float h[V];
-  __shared__ uint4 sSpan[V > 4 ? 256 * (V / 4) : 1];
-  if constexpr (V > 4) {
+  if constexpr (STREAM) {
     // Units up to the last whole one: a lane with a whole chunk has all of its own.
+    __shared__ uint4 sSpan[256 * (V / 4)];
     FpSpan<V> span(sSpan, const_cast<float*>(a.h), (q & ~int64_t{63}) * (V / 4), a.n / 4, threadIdx.x);
-    if (a.n >= 4) span.load(h);
+    span.load(h);
   }
   if (e >= a.n) return;
   const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
   if (e + V <= a.n) {
-    if constexpr (V == 4) load_floats<V>(a.h + e, h);
+    if constexpr (!STREAM) load_floats<V>(a.h + e, h);
     const uint4 out = quantize_chunk<F, R>(h, chunk_thr<R, V>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff),
                                            chunk_has_nan<V>(h));
     *reinterpret_cast<chunk_t<F>*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
@@ -728,24 +729,28 @@ __global__ __launch_bounds__(256) void k_requant_scaled(RequantArgs a) {
 }
 
 // Groups of up to 64 chunks (a power of two): one chunk per lane, held in registers
-// between the maximum and the rounding, so the fp32 input is read once. It comes
-// through LDS in whole lines (see FpSpan). 63M entries against two strided reads (5 bytes
-// each): INT8 blocks of 128, hash SR 62.6 -> 54.2 us; INT4 blocks of 16, RTN 59.4 -> 50.3 us.
-template <int F, int R>
+// between the maximum and the rounding, so the fp32 input is read once. Against two reads,
+// E4M3 hash SR, blocks of 128, from a graph: 31M entries of one buffer 30.3 -> 24.2 us, 63M of
+// three in turn (STREAM, see kRequantStream) 64.7 -> 50.3.
+template <int F, int R, bool STREAM>
 __global__ __launch_bounds__(256) void k_requant_chunks(RequantArgs a) {
   const int t = threadIdx.x;
   const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + t;
-  __shared__ uint4 sSpan[256 * 4];
-  FpSpan<16> span(sSpan, const_cast<float*>(a.h), (q & ~int64_t{63}) * 4, a.n / 4, t);
+  const bool live = q * 16 < a.n;  // whole groups are live or dead together
+  const int64_t e = live ? q * 16 : 0;
   float h[16];
-  span.load(h);
+  if constexpr (STREAM) {
+    __shared__ uint4 sSpan[256 * 4];
+    FpSpan<16> span(sSpan, const_cast<float*>(a.h), (q & ~int64_t{63}) * 4, a.n / 4, t);
+    span.load(h);
+  } else {
+    load_floats<16>(a.h + e, h);
+  }
   float m = 0.0f;
 #pragma unroll
   for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[k]));
   const float s = group_scale<F>(__uint_as_float(lane_umax(__float_as_uint(m), a.lanes_per_group)));
   const float rs = recip_scale(s);
-  const bool live = q * 16 < a.n;  // whole groups are live or dead together
-  const int64_t e = live ? q * 16 : 0;
   if (live && (t & (a.lanes_per_group - 1)) == 0) a.scale[q >> a.lpg_shift] = s;
   const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
   const chunk_t<F> out = quantize_any<F, R>(
@@ -754,29 +759,36 @@ __global__ __launch_bounds__(256) void k_requant_chunks(RequantArgs a) {
 }
 
 // Groups of NT * 16 * CPT entries (e.g. one scale per 64x128 head): one workgroup per
-// group, its values held in registers between the maximum and the rounding. Bound by HBM:
-// each load of a wave covers 1 KiB without gaps and reaches its lane through LDS (E4M3,
-// 63M entries, 315 MB: heads of 8192 entries 55.5 -> 50.6 us; heads of 16384, which one
-// wave each read twice, 51.1 -> 27.5 us for half as many).
-template <int F, int R, int NT, int CPT>
+// group, its values held in registers between the maximum and the rounding. With STREAM
+// (see kRequantStream) each load of a wave covers 1 KiB without gaps and reaches its lane
+// through LDS: bound by HBM, 63M entries of E4M3 (315 MB) in heads of 8192, three buffers in
+// turn, 55.8 -> 50.7 us. Heads of 16384, which one wave each read twice, 99.2 -> 51.6 us.
+template <int F, int R, int NT, int CPT, bool STREAM>
 __global__ __launch_bounds__(NT) void k_requant_group_wg(RequantArgs a) {
   const int t = threadIdx.x;
   const int64_t c0 = static_cast<int64_t>(blockIdx.x) * (NT * CPT);  // the group's first chunk
   const int64_t e0 = c0 * 16;
-  __shared__ uint4 sSpan[NT * 4];
-  FpSpan<16> span(sSpan, const_cast<float*>(a.h), (c0 + (t & ~63)) * 4, a.n / 4, t);
-  uint4 u[CPT][4];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j, span.first += NT * 4, span.units -= NT * 4) span.fetch(u[j]);
   float h[CPT][16];
+  if constexpr (STREAM) {
+    __shared__ uint4 sSpan[NT * 4];
+    FpSpan<16> span(sSpan, const_cast<float*>(a.h), (c0 + (t & ~63)) * 4, a.n / 4, t);
+    uint4 u[CPT][4];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j, span.first += NT * 4, span.units -= NT * 4) span.fetch(u[j]);
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      span.distribute(u[j], h[j]);
+      if (j + 1 < CPT) span.wave_sync();  // its units have been read before the next ones replace them
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) load_floats<16>(a.h + e0 + (static_cast<int64_t>(j) * NT + t) * 16, h[j]);
+  }
   float m = 0.0f;
 #pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    span.distribute(u[j], h[j]);
-    if (j + 1 < CPT) span.wave_sync();  // its units have been read before the next ones replace them
+  for (int j = 0; j < CPT; ++j)
 #pragma unroll
     for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[j][k]));
-  }
   constexpr int NW = NT / 64;
   __shared__ uint32_t red[NW];
   const uint32_t mw = lane_umax(__float_as_uint(m), 64);
@@ -1153,59 +1165,67 @@ hipError_t launch_update(const UpdateArgs& a, int format, int rule, int cfg, boo
   }
 }
 
-template <int F>
+template <int F, bool STREAM>
 static hipError_t launch_requant_f(const RequantArgs& a, int rule, hipStream_t s) {
   constexpr int V = Traits<F>::V;
   const int64_t chunks = (a.n + V - 1) / V;
   const unsigned grid = static_cast<unsigned>((chunks + 255) / 256);
   switch (rule) {
-    case kRTN: hipLaunchKernelGGL((k_requant<F, kRTN>), dim3(grid), dim3(256), 0, s, a); break;
-    case kSR: hipLaunchKernelGGL((k_requant<F, kSR>), dim3(grid), dim3(256), 0, s, a); break;
-    case kPHILOX: hipLaunchKernelGGL((k_requant<F, kPHILOX>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_requant<F, kWEYL>), dim3(grid), dim3(256), 0, s, a); break;
+    case kRTN: hipLaunchKernelGGL((k_requant<F, kRTN, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_requant<F, kSR, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_requant<F, kPHILOX, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_requant<F, kWEYL, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }
 
-template <int F, int NT, int CPT>
+template <int F, int NT, int CPT, bool STREAM>
 static hipError_t launch_requant_group_wg(const RequantArgs& a, int rule, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>(a.n / a.group);
+  const dim3 grid(static_cast<unsigned>(a.n / a.group));
   switch (rule) {
-    case kRTN: hipLaunchKernelGGL((k_requant_group_wg<F, kRTN, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
-    case kSR: hipLaunchKernelGGL((k_requant_group_wg<F, kSR, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
-    case kPHILOX: hipLaunchKernelGGL((k_requant_group_wg<F, kPHILOX, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_requant_group_wg<F, kWEYL, NT, CPT>), dim3(grid), dim3(NT), 0, s, a); break;
+    case kRTN: hipLaunchKernelGGL((k_requant_group_wg<F, kRTN, NT, CPT, STREAM>), grid, dim3(NT), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_requant_group_wg<F, kSR, NT, CPT, STREAM>), grid, dim3(NT), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_requant_group_wg<F, kPHILOX, NT, CPT, STREAM>), grid, dim3(NT), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_requant_group_wg<F, kWEYL, NT, CPT, STREAM>), grid, dim3(NT), 0, s, a); break;
   }
   return hipGetLastError();
 }
 
-template <int F>
+template <int F, bool STREAM>
 static hipError_t launch_requant_chunks(const RequantArgs& a, int rule, hipStream_t s) {
   const unsigned grid = static_cast<unsigned>((a.n / 16 + 255) / 256);
   switch (rule) {
-    case kRTN: hipLaunchKernelGGL((k_requant_chunks<F, kRTN>), dim3(grid), dim3(256), 0, s, a); break;
-    case kSR: hipLaunchKernelGGL((k_requant_chunks<F, kSR>), dim3(grid), dim3(256), 0, s, a); break;
-    case kPHILOX: hipLaunchKernelGGL((k_requant_chunks<F, kPHILOX>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_requant_chunks<F, kWEYL>), dim3(grid), dim3(256), 0, s, a); break;
+    case kRTN: hipLaunchKernelGGL((k_requant_chunks<F, kRTN, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    case kSR: hipLaunchKernelGGL((k_requant_chunks<F, kSR, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    case kPHILOX: hipLaunchKernelGGL((k_requant_chunks<F, kPHILOX, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_requant_chunks<F, kWEYL, STREAM>), dim3(grid), dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
+}
+
+// One read of the input, where a group fits a wave or a workgroup; hipErrorNotSupported for
+// the other groups.
+template <int F, bool STREAM>
+static hipError_t launch_requant_once(const RequantArgs& a, int rule, hipStream_t s) {
+  if (a.group <= 1024 && a.lanes_per_group * 16 == a.group) return launch_requant_chunks<F, STREAM>(a, rule, s);
+  switch (a.group) {
+    case 2048: return launch_requant_group_wg<F, 128, 1, STREAM>(a, rule, s);
+    case 4096: return launch_requant_group_wg<F, 256, 1, STREAM>(a, rule, s);
+    case 8192: return launch_requant_group_wg<F, 256, 2, STREAM>(a, rule, s);
+    case 16384: return launch_requant_group_wg<F, 256, 4, STREAM>(a, rule, s);
+    case 32768: return launch_requant_group_wg<F, 512, 4, STREAM>(a, rule, s);
+    default: return hipErrorNotSupported;
+  }
 }
 
 template <int F>
 static hipError_t launch_requant_scaled(const RequantArgs& a, int rule, hipStream_t s) {
   const int64_t n_groups = a.n / a.group;
-  // One read of the input where a group fits a wave or a workgroup; launches of 2^32
-  // threads or more and the other groups take the loop over groups.
+  // Launches of 2^32 threads or more take the loop over groups.
   if (a.n / 16 < 0xFFFFFF00LL) {
-    if (a.group <= 1024 && a.lanes_per_group * 16 == a.group) return launch_requant_chunks<F>(a, rule, s);
-    switch (a.group) {
-      case 2048: return launch_requant_group_wg<F, 128, 1>(a, rule, s);
-      case 4096: return launch_requant_group_wg<F, 256, 1>(a, rule, s);
-      case 8192: return launch_requant_group_wg<F, 256, 2>(a, rule, s);
-      case 16384: return launch_requant_group_wg<F, 256, 4>(a, rule, s);
-      case 32768: return launch_requant_group_wg<F, 512, 4>(a, rule, s);
-      default: break;
-    }
+    const hipError_t e = a.n >= kRequantStream ? launch_requant_once<F, true>(a, rule, s)
+                                               : launch_requant_once<F, false>(a, rule, s);
+    if (e != hipErrorNotSupported) return e;
   }
   const int64_t gpw = 64 / a.lanes_per_group;
   int64_t blocks = (n_groups + 4 * gpw - 1) / (4 * gpw);
@@ -1220,14 +1240,19 @@ static hipError_t launch_requant_scaled(const RequantArgs& a, int rule, hipStrea
   return hipGetLastError();
 }
 
+template <int F>
+static hipError_t launch_requant_16(const RequantArgs& a, int rule, hipStream_t s) {
+  return a.n >= kRequantStream ? launch_requant_f<F, true>(a, rule, s) : launch_requant_f<F, false>(a, rule, s);
+}
+
 hipError_t launch_requant(const RequantArgs& a, int format, int rule, hipStream_t s) {
   switch (format) {
-    case kFP16: return launch_requant_f<kFP16>(a, rule, s);
-    case kBF16: return launch_requant_f<kBF16>(a, rule, s);
+    case kFP16: return launch_requant_16<kFP16>(a, rule, s);
+    case kBF16: return launch_requant_16<kBF16>(a, rule, s);
     case kE4M3: return launch_requant_scaled<kE4M3>(a, rule, s);
     case kINT8: return launch_requant_scaled<kINT8>(a, rule, s);
     case kINT4: return launch_requant_scaled<kINT4>(a, rule, s);
-    default: return launch_requant_f<kFP32>(a, rule, s);
+    default: return launch_requant_f<kFP32, false>(a, rule, s);
   }
 }
 

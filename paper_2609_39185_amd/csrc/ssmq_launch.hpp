@@ -44,6 +44,14 @@ enum UpdateConfig : int {
   kSlab64x4 = 0, kSlab128x4, kSlab256x1, kSlab256x2, kSlab256x4, kSlab512x2, kSlab512x4,
   kSlab1024x4, kSlab1024x8, kRowKernel, kChannelKernel
 };
+// Requantize: entries from which the input streams past the caches (nontemporal loads, in
+// whole lines through LDS). An input of 192 MiB and more does not stay in the 256 MB Infinity
+// Cache beside its codes; a smaller one, just written by the prefill, does, and nontemporal
+// loads give that up. E4M3 Weyl, one scale per 8192 entries, from a graph, plain / streaming
+// loads: 31M entries of one buffer 23.6 / 26.7 us, of three buffers in turn 29.4 / 26.7, 63M
+// of one 49.8 / 50.8, of three 55.8 / 50.8; written by the kernel before it, both together,
+// 14.7M 30.7 / 33.3, 31M 59.2 / 63.5, 63M 114 / 121.
+constexpr int64_t kRequantStream = int64_t{3} << 24;
 constexpr int kSlabThreads[] = {64, 128, 256, 256, 256, 512, 512, 1024, 1024};
 constexpr int kSlabChunks[] = {4, 4, 1, 2, 4, 2, 4, 4, 8};
 constexpr int kMaxDstate = 1024;  // 64 lanes x 16 E4M3 entries per row

@@ -149,9 +149,12 @@ def test_conv1d_paths(ssmq, b, c, width, shift, act, bias):
     ("fp16", "philox", 0, 4101), ("int8", "weyl", 16, 16 * 65), ("int4", "sr", 128, 128 * 33),
     ("e4m3", "weyl", 1024, 1024 * 5), ("int8", "rtn", 2048, 2048 * 3), ("e4m3", "philox", 4096, 4096),
     ("int4", "weyl", 8192, 8192 * 2), ("e4m3", "sr", 16384, 16384 * 3), ("int8", "weyl", 32768, 32768 * 2)])
-def test_requantize_spans(ssmq, fmt, rule, group, n):
+@pytest.mark.parametrize("special", [False, True])
+def test_requantize_spans(ssmq, fmt, rule, group, n, special):
     say(f"case requantize span {fmt} {rule} g{group} n {n}")
     x = (np.random.default_rng(n).standard_normal(n) * 0.3).astype(np.float32)
+    if special:  # the first group is NaN and infinite, the second holds a NaN, the last tiny values
+        x[0], x[n // 2], x[n - 1], x[1:2] = np.nan, np.nan, -1e-40, -np.inf
     per = 2 if fmt == "int4" else 1
     codes = Guarded(torch.zeros(n // per, dtype=wl.CODE_TORCH_DTYPE[fmt]))
     sc = Guarded(torch.zeros(n // group)) if group else None
@@ -162,7 +165,7 @@ def test_requantize_spans(ssmq, fmt, rule, group, n):
     got = wl.to_numpy_codes(fmt, codes.check("codes"))
     assert np.array_equal(got.ravel(), np.asarray(want).ravel())
     if sc:
-        assert np.array_equal(sc.check("scale").numpy(), wsc)
+        assert np.array_equal(sc.check("scale").numpy(), wsc, equal_nan=True)
 
 
 # head slabs whose lanes per row are constant (rows of 4, 8 and 16 lanes; a group per row or
@@ -236,3 +239,40 @@ def test_channels_same_as_rows(ssmq, fmt, group, rule, b, h, fused):
         assert torch.equal(one.cpu(), got[s]), i
         assert torch.equal(y1.cpu().nan_to_num(7.0), gy[s].nan_to_num(7.0)), i
         assert not group or torch.equal(sc1.cpu(), gsc[i]), i
+
+
+# inputs of 48M entries and more, which stream: ragged ends, infinities and NaN, against calls
+# on pieces of them (which load plainly), bit for bit
+@pytest.mark.parametrize("fmt,rule,group,extra", [
+    ("fp16", "weyl", 0, 0), ("fp16", "sr", 0, 3), ("bf16", "philox", 0, 520 + 4), ("bf16", "rtn", 0, 2051),
+    ("int8", "weyl", 16, 16 * 65), ("int4", "sr", 128, 128 * 33), ("e4m3", "philox", 1024, 1024),
+    ("e4m3", "weyl", 2048, 2048 * 3), ("int8", "rtn", 4096, 0), ("int4", "weyl", 8192, 8192),
+    ("e4m3", "sr", 16384, 16384), ("int4", "rtn", 32768, 32768)])
+def test_requantize_stream_same_as_pieces(ssmq, fmt, rule, group, extra):
+    n = (3 << 24) + extra
+    say(f"case requantize stream {fmt} {rule} g{group} n {n}")
+    g = torch.Generator(device=DEV).manual_seed(n)
+    x = torch.randn(n, generator=g, device=DEV) * 0.3
+    x[torch.randint(n, (64,), generator=g, device=DEV)] = float("nan")
+    x[torch.randint(n, (64,), generator=g, device=DEV)] = -float("inf")
+    x[0], x[n - 1], x[n // 2] = float("inf"), float("nan"), 1e-40
+    per = 2 if fmt == "int4" else 1
+    q = {"rule": rule, "fmt": fmt, "scale_group": group, "seed": 2, "layer": 3, "step": 9, "dither_block": 16}
+    codes = torch.full((n // per + GUARD,), 77, dtype=wl.CODE_TORCH_DTYPE[fmt], device=DEV)
+    sc = torch.full((n // group + GUARD,), 77.0, device=DEV) if group else None
+    ssmq.requantize(x, codes[:n // per], sc[:n // group] if group else None, **q)
+    piece = 5 * (1 << 22) + (group or 16)
+    piece -= piece % (group or 16)
+    one, sc1 = torch.zeros_like(codes[:n // per]), torch.zeros_like(sc[:n // group]) if group else None
+    for i in range(0, n, piece):
+        k = min(i + piece, n)
+        part, out = x[i:k].clone(), torch.zeros_like(one[i // per:k // per])
+        s1 = torch.zeros_like(sc1[i // group:k // group]) if group else None
+        ssmq.requantize(part, out, s1, entry_base=i, **q)
+        one[i // per:k // per] = out
+        if group:
+            sc1[i // group:k // group] = s1
+    assert torch.equal(codes[:n // per], one) and bool((codes[n // per:] == 77).all())
+    if group:
+        assert torch.equal(sc[:n // group].view(torch.int32), sc1.view(torch.int32))
+        assert bool((sc[n // group:] == 77).all())
