@@ -1282,7 +1282,12 @@ static hipError_t launch_replay_e(const ReplayArgs& a, int rule, int threads, hi
 
 template <int F>
 static hipError_t launch_replay_f(const ReplayArgs& a, int rule, hipStream_t s) {
-  if (a.n < kReplayShort && a.lanes_per_group <= 32) {  // groups of 256 entries need four per lane
+  // Groups of 256 entries need four per lane. Philox makes its thresholds for four entries at a
+  // time, twice the work for two per lane: INT8 and INT4, whose rounding is short enough for that
+  // to show, take the short form only up to half that size (INT8 blocks of 128, 64 steps: 262k
+  // entries 49.7 us with four, 48.3 with two; 400k 62.9 and 69.9).
+  const int64_t most = rule == kPHILOX && is_int_fmt<F> ? kReplayShort / 2 : kReplayShort - 1;
+  if (a.n <= most && a.lanes_per_group <= 32) {
     ReplayArgs b = a;
     if (Traits<F>::scaled) b.lanes_per_group *= 2;
     return launch_replay_e<F, 2, 4>(b, rule, 64, s);

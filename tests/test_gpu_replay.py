@@ -143,7 +143,9 @@ def test_replay_full_layer_sampled(ssmq):
     ("e4m3", 128, "weyl", 128 * 3, 8), ("fp32", 0, "rtn", 132, 3),
     ("int4", 16, "weyl", 2 ** 19 - 16, 2), ("fp16", 0, "sr", 2 ** 19 + 12, 3),
     ("bf16", 0, "philox", 2 ** 19, 2), ("e4m3", 16, "philox", 2 ** 19 + 48, 3),
-    ("int4", 4, "sr", 2 ** 19 + 4, 2), ("fp32", 0, "weyl", 2 ** 19 + 1024, 1)])
+    ("int4", 4, "sr", 2 ** 19 + 4, 2), ("fp32", 0, "weyl", 2 ** 19 + 1024, 1),
+    # Philox in the integer formats: two per lane up to 2^18 entries, four from there
+    ("int8", 16, "philox", 2 ** 18, 3), ("int4", 8, "philox", 2 ** 18 + 8, 2)])
 def test_replay_lengths(ssmq, fmt, group, rule, n, T):
     h0, a, w = _traces(n, T, seed=n % 1000)
     say(f"case replay {fmt} {rule} group {group}: n {n}, T {T}")
