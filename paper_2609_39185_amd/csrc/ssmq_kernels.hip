@@ -683,47 +683,36 @@ __global__ __launch_bounds__(256) void k_requant(RequantArgs a) {
 
 // ---------------------------------------------------------------------------
 // Requantize to a scaled format (E4M3, INT8, INT4) with group scales.
-// lanes_per_group lanes (a power of two <= 64) work on one group; a wave covers
-// 64 / lanes_per_group groups per iteration and loops over each group's
-// 16-entry chunks.
 // ---------------------------------------------------------------------------
+// Groups that fit neither a wave's chunks nor a workgroup's (48, 1536, 65536 entries): one
+// wave per group loops over its 16-entry chunks twice, for the maximum and for the rounding.
 template <int F, int R>
 __global__ __launch_bounds__(256) void k_requant_scaled(RequantArgs a) {
   const int lane = threadIdx.x & 63;
-  const int LG = a.lanes_per_group;
-  const int gpw = 64 / LG;
-  const int sub = lane / LG;
-  const int li = lane & (LG - 1);
   const int64_t chunks_per_group = a.group / 16;
   const int64_t n_groups = a.n / a.group;
   const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * 4;
-  for (int64_t g0 = wave * gpw; g0 < n_groups; g0 += nwaves * gpw) {
-    const int64_t grp = g0 + sub;
-    const bool live = grp < n_groups;
+  for (int64_t grp = wave; grp < n_groups; grp += nwaves) {
     float m = 0.0f;
-    if (live) {
-      for (int64_t c = li; c < chunks_per_group; c += LG) {
-        float h[16];
-        load_floats<16>(a.h + grp * a.group + c * 16, h);
+    for (int64_t c = lane; c < chunks_per_group; c += 64) {
+      float h[16];
+      load_floats<16>(a.h + grp * a.group + c * 16, h);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[k]));
-      }
+      for (int k = 0; k < 16; ++k) m = fmaxf(m, __builtin_fabsf(h[k]));
     }
-    const float s = group_scale<F>(__uint_as_float(lane_umax(__float_as_uint(m), LG)));
+    const float s = group_scale<F>(__uint_as_float(lane_umax(__float_as_uint(m), 64)));
     const float rs = recip_scale(s);
-    if (live && li == 0) a.scale[grp] = s;
-    const int64_t iters = (chunks_per_group + LG - 1) / LG;  // uniform trip count
-    for (int64_t it = 0; it < iters; ++it) {
-      const int64_t c = it * LG + li;
-      const bool ok = live && c < chunks_per_group;
-      const int64_t e = (ok ? grp * a.group + c * 16 : 0);
+    if (lane == 0) a.scale[grp] = s;
+    for (int64_t c0 = 0; c0 < chunks_per_group; c0 += 64) {  // uniform trip count
+      const bool live = c0 + lane < chunks_per_group;
+      const int64_t e = grp * a.group + (live ? c0 + lane : 0) * 16;
       float h[16];
       load_floats<16>(a.h + e, h);
       const uint64_t ge = a.entry_base + static_cast<uint64_t>(e);
       const chunk_t<F> out = quantize_any<F, R>(h, rs, chunk_thr<R, 16>(ge, a.thr, thr_base<R>(ge, a.thr), a.toff),
                                                 chunk_has_nan<16>(h));
-      if (ok) *reinterpret_cast<chunk_t<F>*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
+      if (live) *reinterpret_cast<chunk_t<F>*>(static_cast<uint8_t*>(a.codes) + chunk_bytes_at<F>(e)) = out;
     }
   }
 }
@@ -1227,8 +1216,7 @@ static hipError_t launch_requant_scaled(const RequantArgs& a, int rule, hipStrea
                                                : launch_requant_once<F, false>(a, rule, s);
     if (e != hipErrorNotSupported) return e;
   }
-  const int64_t gpw = 64 / a.lanes_per_group;
-  int64_t blocks = (n_groups + 4 * gpw - 1) / (4 * gpw);
+  int64_t blocks = (n_groups + 3) / 4;
   if (blocks > 65536) blocks = 65536;
   const unsigned grid = static_cast<unsigned>(blocks);
   switch (rule) {

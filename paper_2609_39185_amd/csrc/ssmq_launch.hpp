@@ -101,7 +101,7 @@ struct RequantArgs {
   float* scale;
   int64_t n;
   int64_t group;            // E4M3 entries per scale
-  int32_t lanes_per_group;  // E4M3 lanes cooperating on one group
+  int32_t lanes_per_group;  // groups of up to 64 chunks (a power of two): lanes of one group
   int32_t lpg_shift;        // log2(lanes_per_group)
   uint64_t entry_base;
   Thr thr;

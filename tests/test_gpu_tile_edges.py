@@ -148,7 +148,10 @@ def test_conv1d_paths(ssmq, b, c, width, shift, act, bias):
     ("fp16", "weyl", 0, 3), ("bf16", "sr", 0, 13), ("fp16", "rtn", 0, 520), ("bf16", "weyl", 0, 2051),
     ("fp16", "philox", 0, 4101), ("int8", "weyl", 16, 16 * 65), ("int4", "sr", 128, 128 * 33),
     ("e4m3", "weyl", 1024, 1024 * 5), ("int8", "rtn", 2048, 2048 * 3), ("e4m3", "philox", 4096, 4096),
-    ("int4", "weyl", 8192, 8192 * 2), ("e4m3", "sr", 16384, 16384 * 3), ("int8", "weyl", 32768, 32768 * 2)])
+    ("int4", "weyl", 8192, 8192 * 2), ("e4m3", "sr", 16384, 16384 * 3), ("int8", "weyl", 32768, 32768 * 2),
+    # a wave per group: a part of its lanes, one chunk more than it has lanes, beyond a workgroup
+    ("e4m3", "rtn", 48, 48 * 5), ("int4", "sr", 1040, 1040 * 9), ("int8", "weyl", 1536, 1536),
+    ("int8", "philox", 65536, 65536 * 2)])
 @pytest.mark.parametrize("special", [False, True])
 def test_requantize_spans(ssmq, fmt, rule, group, n, special):
     say(f"case requantize span {fmt} {rule} g{group} n {n}")
