@@ -168,7 +168,8 @@ def test_int_full_size_hybrid_layer(ssmq):
 
 
 @pytest.mark.parametrize("fmt", ["int8", "int4", "e4m3"])
-def test_group_scales_over_all_binades(ssmq, fmt):
+@pytest.mark.parametrize("rule", ["weyl", "rtn", "sr"])
+def test_group_scales_over_all_binades(ssmq, fmt, rule):
     """Group maxima from 2^-126 to FLT_MAX (both sides of the fast division's range,
     infinity and flushed groups): scales and codes bit-exact against the oracle. This
     exercises the scale division and the reciprocal of every group."""
@@ -187,10 +188,10 @@ def test_group_scales_over_all_binades(ssmq, fmt):
     per = 2 if fmt == "int4" else 1
     codes = torch.zeros((x.size // per,), dtype=torch.uint8, device=DEV)
     scale = torch.zeros((n_groups,), dtype=torch.float32, device=DEV)
-    ssmq.requantize(h, codes, scale, rule="weyl", fmt=fmt, scale_group=group, step=4, layer=1,
+    ssmq.requantize(h, codes, scale, rule=rule, fmt=fmt, scale_group=group, step=4, layer=1,
                     dither_block=16)
     torch.cuda.synchronize()
-    want, wscale = oracle.requantize(fmt, "weyl", x, step=4, layer=1, block=16, group=group)
+    want, wscale = oracle.requantize(fmt, rule, x, step=4, layer=1, block=16, group=group)
     np.testing.assert_array_equal(scale.cpu().numpy(), wscale)
     got = codes.cpu().numpy()
     assert np.array_equal(got, want), np.nonzero(got != want)[0][:10]

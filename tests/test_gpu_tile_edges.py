@@ -279,3 +279,64 @@ def test_requantize_stream_same_as_pieces(ssmq, fmt, rule, group, extra):
     if group:
         assert torch.equal(sc[:n // group].view(torch.int32), sc1.view(torch.int32))
         assert bool((sc[n // group:] == 77).all())
+
+
+# infinities and NaN in some rows of a step and of a checkpoint write, in the row kernel and the
+# head slabs: the same codes, scales and non-finite outputs as the oracle, the other rows unharmed
+@pytest.mark.parametrize("fp32_state", [False, True])
+@pytest.mark.parametrize("family,shape", [("mamba1", (3, 107, 1, 16, 1)), ("mamba2", (2, 3, 5, 128, 1)),
+                                          ("mamba2", (2, 3, 64, 128, 1))])
+@pytest.mark.parametrize("fmt,group,rule", [("fp16", 0, "weyl"), ("bf16", 0, "rtn"), ("e4m3", 16, "sr"),
+                                            ("int8", 16, "rtn"), ("int8", 16, "weyl"), ("int4", 16, "rtn"),
+                                            ("int4", 16, "philox")])
+def test_non_finite_rows(ssmq, fmt, group, rule, family, shape, fp32_state):
+    b, h, p, n, g = shape
+    say(f"case non-finite {family} {fmt} {rule} {shape} fp32 state {fp32_state}")
+    A, D = wl.layer_params(family, h, n, 590)
+    x, dt, B, C = wl.step_inputs(b, h, p, n, g, 591)
+    rows = x.view(-1)
+    k = rows.numel()
+    rows[0], rows[k // 3], rows[k - 1], rows[k // 2] = float("inf"), float("nan"), -float("inf"), 1e30
+    a = [v.to(DEV) for v in (x, dt, A, B, C, D)]
+    o = [v.numpy() for v in (x, dt, A, B, C, D)]
+    y = torch.zeros((b, h, p), device=DEV)
+    q = {"step": 5, "layer": 1}
+    if fp32_state:
+        h0 = (np.random.default_rng(592).standard_normal((b, h, p, n)) * 0.3).astype(np.float32)
+        st = torch.from_numpy(h0).to(DEV)
+        sc = torch.zeros(h0.size // group, device=DEV) if group else None
+        ssmq.state_update(st, sc, *a, y, rule=rule, fmt=fmt, scale_group=group, fp32_state=True, **q)
+        want, wsc, wy = oracle.state_update_fp32_grid(fmt, rule, h0, *o, block=16, group=group, **q)
+    else:
+        codes, scale = wl.initial_state(fmt, b, h, p, n, 592, group=group)
+        st, sc = codes.to(DEV), None if scale is None else scale.to(DEV)
+        ssmq.state_update(st, sc, *a, y, rule=rule, fmt=fmt, scale_group=group, **q)
+        want, wsc, wy, _ = oracle.state_update(fmt, rule, wl.to_numpy_codes(fmt, codes),
+                                               None if scale is None else scale.numpy(), *o, block=16,
+                                               group=group, **q)
+    torch.cuda.synchronize()
+
+    def same(got, ref, what):  # non-finite values agree; finite ones to 1e-5
+        got, ref = np.asarray(got, np.float64).ravel(), np.asarray(ref, np.float64).ravel()
+        f = np.isfinite(ref)
+        assert np.array_equal(got[~f], ref[~f], equal_nan=True), what
+        assert int(np.sum(~np.isfinite(got[f]))) == 0, what
+        return f, got, ref
+
+    bar = Bar(fmt, f"non-finite {fmt} {rule}")
+    if group:
+        f, gs, ws = same(sc.cpu().numpy(), wsc, "scale")
+        bar.scales(gs[f], ws[f])
+    f, gy, ry = same(y.cpu().numpy(), wy, "y")
+    assert f.any() and not f.all()
+    assert np.all(np.abs(gy[f] - ry[f]) <= 1e-4 * (1 + np.abs(ry[f])))  # held to the bar elsewhere
+    if fp32_state:
+        got = st.cpu().numpy()
+        f, _, _ = same(got, want, "state")
+        gf, wf = np.where(f, got.ravel(), 0), np.where(f, np.asarray(want).ravel(), 0)
+        one = lambda s: np.where(np.isfinite(s), s, 0) if group else None
+        bar.codes(_codes_of(fmt, gf, one(sc.cpu().numpy()) if group else None, group),
+                  _codes_of(fmt, wf, one(np.asarray(wsc)) if group else None, group))
+    else:
+        bar.codes(wl.to_numpy_codes(fmt, st), want)
+    bar.check()
