@@ -701,11 +701,12 @@ __device__ inline float recip_scale(float s) {
 // would wrap (the result is 0 or infinity there):
 //   exp_values        k = rint(z log2 e), r = z - k ln 2 (ln 2 in two doubles), exp(r)
 //                     on |r| <= ln 2 / 2 by a degree-11 minimax polynomial (Remez
-//                     exchange, relative error 2^-53.7): 17 double operations.
+//                     exchange, relative error 2^-53.7): 17 double operations, for
+//                     lanes that take several.
 //   exp_values_table  k = rint(z 256 / ln 2), 2^(k mod 256 / 256) from a table in LDS
 //                     and exp(r) - 1 on |r| <= ln 2 / 512 by its Taylor polynomial of
 //                     degree 4 (relative error 2^-54.5): 11 double operations, for
-//                     kernels that take many.
+//                     workgroups that take several thousand.
 // A double operation issues in as many cycles as a three-operand fp32 one (4.7 at a
 // nominal 2.4 GHz), and the library's exp takes about 20 and branches.
 // ---------------------------------------------------------------------------
@@ -734,36 +735,23 @@ __device__ inline void exp_out_of_range(const float (&z)[N], float (&out)[N]) {
     }
   }
 }
-// p = fma(p, r, c), c in a scalar register pair: left to itself the compiler takes the
-// two-operand form, which overwrites its addend, and copies c into vector registers
-// for every term.
-__device__ inline double fma_s(double p, double r, double c) {
-  double d;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(r), "s"(c));
-  return d;
-}
-// SCALAR: the coefficients stay in scalar registers (fma_s), which suits one exponential
-// among other work (the head slabs, one per head: E4M3 Weyl 108.9 us per layer against
-// 109.5); a lane's many share the copies that the two-operand form makes.
-template <bool SCALAR>
 __device__ inline float exp_in_range(float zf) {
-  auto f = [](double p, double r, double c) { return SCALAR ? fma_s(p, r, c) : __builtin_fma(p, r, c); };
   const double z = static_cast<double>(zf);
   const double t = __builtin_fma(z, 0x1.71547652b82fep+0, 0x1.8p52);  // k in the low bits
   const uint32_t k = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, t));
   const double kd = t - 0x1.8p52;
   double r = __builtin_fma(kd, -0x1.62e42fefa39efp-1, z);
   r = __builtin_fma(kd, -0x1.abc9e3b39803fp-56, r);
-  double p = f(r, 0x1.8ad0f40784e9dp-26, 0x1.28a2c68333593p-22);
-  p = f(p, r, 0x1.71f6152e4b934p-19);
-  p = f(p, r, 0x1.a019a66a00698p-16);
-  p = f(p, r, 0x1.a019f62058ba4p-13);
-  p = f(p, r, 0x1.6c16c17f41b14p-10);
-  p = f(p, r, 0x1.111111137ba72p-7);
-  p = f(p, r, 0x1.55555555520c1p-5);
-  p = f(p, r, 0x1.555555555481ap-3);
-  p = f(p, r, 0x1.0000000000005p-1);
-  p = f(p, r, 0x1.0000000000003p+0);
+  double p = __builtin_fma(r, 0x1.8ad0f40784e9dp-26, 0x1.28a2c68333593p-22);
+  p = __builtin_fma(p, r, 0x1.71f6152e4b934p-19);
+  p = __builtin_fma(p, r, 0x1.a019a66a00698p-16);
+  p = __builtin_fma(p, r, 0x1.a019f62058ba4p-13);
+  p = __builtin_fma(p, r, 0x1.6c16c17f41b14p-10);
+  p = __builtin_fma(p, r, 0x1.111111137ba72p-7);
+  p = __builtin_fma(p, r, 0x1.55555555520c1p-5);
+  p = __builtin_fma(p, r, 0x1.555555555481ap-3);
+  p = __builtin_fma(p, r, 0x1.0000000000005p-1);
+  p = __builtin_fma(p, r, 0x1.0000000000003p+0);
   p = __builtin_fma(p, r, 1.0);
   return static_cast<float>(add_exponent<20>(p, k));
 }
@@ -774,9 +762,10 @@ __device__ inline float exp_in_range(float zf) {
 template <int N>
 __device__ inline void exp_values(const float (&z)[N], float (&out)[N]) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) out[i] = exp_in_range<N == 1>(z[i]);
+  for (int i = 0; i < N; ++i) out[i] = exp_in_range(z[i]);
   exp_out_of_range<N>(z, out);
 }
+// One alone, as the exhaustive check takes it too.
 __device__ inline float exp_value(float zf) {
   const float z[1] = {zf};
   float out[1];
@@ -844,6 +833,14 @@ __device__ const uint64_t kExpTableBits[kExpTable] = {
 // Copies the table to LDS (a barrier of the caller's has to follow).
 __device__ inline void stage_exp_table(double* tab, int t, int threads) {
   for (int i = t; i < kExpTable; i += threads) tab[i] = __builtin_bit_cast(double, kExpTableBits[i]);
+}
+// p = fma(p, r, c), c in a scalar register pair: left to itself the compiler takes the
+// two-operand form, which overwrites its addend, and copies c into vector registers
+// for every term.
+__device__ inline double fma_s(double p, double r, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(r), "s"(c));
+  return d;
 }
 template <int N>
 __device__ inline void exp_values_table(const double* tab, const float (&z)[N], float (&out)[N]) {

@@ -40,8 +40,12 @@ __device__ inline void load_floats(const float* p, float (&out)[V]) {
   }
 }
 
-// dA = fl32(exp(fl32(dt A))), correctly rounded.
-__device__ inline float decay(float dtv, float a) { return exp_value(dtv * a); }
+// dA = fl32(exp(fl32(dt A))), correctly rounded. One per lane or per head: the library's exp,
+// rounded once, is no slower there than the forms of ssmq_device.hpp (same bits), which serve
+// lanes that take many.
+__device__ inline float decay(float dtv, float a) {
+  return static_cast<float>(exp(static_cast<double>(dtv * a)));
+}
 template <int N>
 __device__ inline void decays(float dtv, const float (&a)[N], float (&dA)[N]) {
   float z[N];
