@@ -256,14 +256,17 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
     cfg = ssmq::kRowKernel;
     a.lanes_per_group = scaled ? static_cast<int32_t>(group / 16) : 1;
     // The channel kernel's set-up (the exp table, B, C and step sizes staged, a barrier) pays from
-    // about a million chunks on and where a workgroup takes several sequences. From a graph, Weyl,
-    // row kernel / channel kernel: INT8 1 x 1536 channels 3.54 / 3.85 us, 64 x 5120 7.7 / 8.5,
-    // 192 x 5120 18.1 / 19.0, 225 x 5120 22.5 / 21.4, 400 x 8192 59.1 / 52.6; bf16 (two chunks per
-    // channel) 1 x 5120 2.91 / 3.21, 64 x 5120 7.9 / 8.0, 100 x 5120 10.7 / 10.1, 225 x 5120
-    // 23.2 / 22.0. fp32 (four chunks) takes the row kernel at every size: 16 x 5120 3.84 / 4.20,
-    // 225 x 5120 30.9 / 32.4, 400 x 8192 84.7 / 88.0 us.
+    // about 400000 rows on (one per channel and sequence) and where workgroups take several
+    // sequences; in the scaled formats under hash SR and Philox, whose generators fill its
+    // registers, from a million. From a graph, three states in turn, Weyl, row kernel / channel
+    // kernel: INT8 1 x 1536 channels 3.54 / 3.85 us, 64 x 5120 8.3 / 8.9, 100 x 4096 10.6 / 10.2,
+    // 225 x 5120 23.6 / 22.8; bf16 1 x 1536 2.86 / 3.16, 64 x 5120 9.0 / 9.2, 100 x 4096 10.4 / 9.7,
+    // 172 x 5120 19.6 / 18.8; INT8 hash SR 100 x 4096 11.7 / 12.2, 225 x 5120 26.0 / 26.8, 400 x 8192
+    // 68 / 64. An fp32 state, four lanes a row, takes the row kernel at every size: 16 x 5120
+    // 3.99 / 4.25, 172 x 5120 25.5 / 27.9, 225 x 5120 32.3 / 34.9 us.
+    const bool generator = scaled && (q->rule == SSMQ_SR || q->rule == SSMQ_SR_PHILOX);
     if (d.a_per_state && d.headdim == 1 && d.dstate == ssmq::kChannelN && d.ngroups == 1 && !fp32_state &&
-        q->format != SSMQ_FP32 && a.n_chunks >= ssmq::kChannelChunks) {
+        q->format != SSMQ_FP32 && bh >= (generator ? ssmq::kChannelRowsDither : ssmq::kChannelRows)) {
       const int64_t tiles = (static_cast<int64_t>(d.nheads) * a.lanes_per_row + 255) / 256;
       // The batch is split evenly over as many workgroups as run at once (four per CU, five
       // for the 16-bit formats, by registers), or twice, three times that many where one
@@ -274,7 +277,7 @@ ssmq_status ssmq_state_update_ex(const ssmq_dims* dims, const ssmq_qparams* q,
       const int64_t least = (d.batch + ssmq::kChannelBatch - 1) / ssmq::kChannelBatch;
       int64_t parts = turns * fit / tiles;
       if (parts < least) parts = least;
-      if (parts <= 65535 && 2 * parts <= d.batch) {
+      if (parts <= 65535 && parts < d.batch) {
         cfg = ssmq::kChannelKernel;
         a.batch_per_wg = static_cast<int32_t>(d.batch / parts);
         a.batch_rem = static_cast<int32_t>(d.batch % parts);

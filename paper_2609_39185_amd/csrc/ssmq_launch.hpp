@@ -57,7 +57,8 @@ constexpr int kSlabChunks[] = {4, 4, 1, 2, 4, 2, 4, 4, 8};
 constexpr int kMaxDstate = 1024;  // 64 lanes x 16 E4M3 entries per row
 constexpr int kChannelN = 16;      // channel kernel: entries per row ...
 constexpr int kChannelBatch = 8;   // ... the most sequences per workgroup ...
-constexpr int64_t kChannelChunks = 1000000;  // ... and the fewest chunks of a state that takes it
+constexpr int64_t kChannelRows = 400000;       // ... and the fewest rows of a state that takes it;
+constexpr int64_t kChannelRowsDither = 1000000;  // scaled formats under hash SR and Philox
 
 struct UpdateArgs {
   void* state;
