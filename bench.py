@@ -61,7 +61,8 @@ def parse_args():
                     help="--state-error: also run checkpointed rules, rounding every k-th write")
     ap.add_argument("--entry-points", action="store_true",
                     help="instead of the fused step: ssmq_requantize and ssmq_dither_fill on one "
-                         "layer's entries (GB/s of their own reads and writes)")
+                         "layer's entries (GB/s of their own reads and writes), checkpoint writes of "
+                         "a quarter of it and steps of a large Mamba-1 batch")
     ap.add_argument("--replay", action="store_true",
                     help="instead of throughput: open-loop replay of synthetic recorded traces")
     ap.add_argument("--rp-batch", type=int, default=0,
@@ -92,6 +93,9 @@ def parse_args():
                          "FETCH_SIZE, then --pmc WRITE_SIZE) into the summaries under profiles/")
     ap.add_argument("--summarize-entry-trace", metavar="TRACE_DIR",
                     help="write the entry-point kernel trace summary under profiles/")
+    ap.add_argument("--summarize-entry-valu", metavar="PMC_DIR",
+                    help="write the vector-instruction counters of --entry-points' Mamba-1 and "
+                         "checkpoint kernels under profiles/")
     ap.add_argument("--summarize-trace", nargs=2, metavar=("TRACE_DIR", "NAME"),
                     help="turn a rocprofv3 --kernel-trace --stats run of --replay into "
                          "profiles/NAME.kernel_trace.md")
@@ -150,6 +154,8 @@ def main() -> int:
         return summarize_replay_trace(*args.summarize_trace)
     if args.summarize_entry_trace:
         return summarize_entry_points_trace(args.summarize_entry_trace)
+    if args.summarize_entry_valu:
+        return summarize_entry_points_valu(args.summarize_entry_valu)
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:
         print(json.dumps({"error": "this benchmark measures one GPU only; the state update shards "
@@ -1046,14 +1052,13 @@ def summarize_replay_trace(trace_dir: str, name: str) -> int:
              "Command (repository root as $R, an output directory as $OUT, run from /tmp with TMPDIR=/tmp):", "",
              f"    {PROFILE_COMMANDS['replay_trace']}",
              f"    {PROFILE_COMMANDS['replay_trace_summary']}", "",
-             "The longest call of each instance is a full-size launch: the RTN instances also run "
-             "one untimed 256-entry, one-step launch, the hash-SR instances run twice at full size "
-             "(seeds 0 and 1). Trace rate = 8 B x entries x steps / the full-size duration.", "",
+             "The longest call of each instance is a full-size launch: the hash-SR instances run twice "
+             "at full size (seeds 0 and 1). Trace rate = 8 B x entries x steps / the full-size duration.", "",
              "| kernel | format:rule | calls | full-size launch us | trace GB/s |",
              "|---|---|---|---|---|"]
     for r in sorted(stats, key=lambda r: r["Name"]):
         km = re.search(r"k_replay<(\d+), (\d+)", r["Name"])
-        if not km:
+        if not km or re.search(r"k_replay<\d+, \d+, 2, ", r["Name"]):  # the form for short states
             continue
         key = f"{fmts[int(km.group(1))]}:{rules[int(km.group(2))]}"
         mx = float(r["MaxNs"]) / 1e3
@@ -1069,25 +1074,63 @@ def summarize_replay_trace(trace_dir: str, name: str) -> int:
 def summarize_entry_points_trace(trace_dir: str) -> int:
     """Write profiles/entry_points.hybrid_m2_stack.kernel_trace.md from a kernel
     trace of `bench.py --entry-points` (PROFILE_COMMANDS["entry_trace"]): per
-    requantize and threshold-fill kernel instance, calls and durations."""
+    kernel instance of its calls, calls and durations."""
     import re
 
     stats = _csv_rows(trace_dir, "kernel_stats.csv")
-    lines = ["# Kernel trace of the requantize and threshold-fill calls (268,435,456 entries per launch)", "",
+    lines = ["# Kernel trace of the requantize and threshold-fill calls (268,435,456 entries per launch), of "
+             "checkpoint writes (67,108,864 entries) and of Mamba-1 steps (18,432,000 entries)", "",
              "Command (repository root as $R, an output directory as $OUT, run from /tmp with TMPDIR=/tmp):", "",
              f"    {PROFILE_COMMANDS['entry_trace']}",
              f"    {PROFILE_COMMANDS['entry_trace_summary']}", "",
              "Template arguments: format code (0 fp16, 1 bf16, 2 E4M3, 4 INT8, 5 INT4), rule code "
-             "(0 RTN, 1 hash SR, 2 Weyl, 3 Philox), and for the per-group kernel the threads and the chunks per thread.", "",
+             "(0 RTN, 1 hash SR, 2 Weyl, 3 Philox); for the requantize kernels whether the input streams past "
+             "the caches (the per-group kernel has the threads and the chunks per thread before it); for the row "
+             "kernel A per state and the fp32 state of a checkpoint write.", "",
              "| kernel | calls | avg us | min us | max us |", "|---|---|---|---|---|"]
     for r in sorted(stats, key=lambda r: r["Name"]):
-        if not re.search(r"k_requant|k_dither_fill", r["Name"]):
+        if not re.search(r"k_requant|k_dither_fill|k_update_", r["Name"]):
             continue
         lines.append(f"| `{_short_kernel(r['Name'])}` "
                      f"| {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
                      f"{float(r['MaxNs']) / 1e3:.1f} |")
     os.makedirs(PROFILE_DIR, exist_ok=True)
     with open(os.path.join(PROFILE_DIR, "entry_points.hybrid_m2_stack.kernel_trace.md"), "w") as f:
+        f.write("\n".join(lines) + "\n")
+    print("\n".join(lines))
+    return 0
+
+
+def summarize_entry_points_valu(pmc_dir: str) -> int:
+    """Write profiles/k_update_channels.m1_b225.valu.md from the counters of `bench.py
+    --entry-points` (PROFILE_COMMANDS["entry_valu"]): per Mamba-1 and checkpoint kernel
+    instance, waves, vector instructions per entry and the VALU busy fraction."""
+    import statistics
+    from collections import defaultdict
+
+    agent = [r for r in _csv_rows(pmc_dir, "agent_info.csv") if r.get("Agent_Type") == "GPU"][0]
+    simds, xcc = int(agent["Simd_Count"]), int(agent["Num_Xcc"])
+    vals = defaultdict(lambda: defaultdict(list))
+    for r in _csv_rows(pmc_dir, "counter_collection.csv"):
+        if _variant_of(r["Kernel_Name"]) is not None:
+            vals[r["Kernel_Name"]][r["Counter_Name"]].append(float(r["Counter_Value"]))
+    lines = ["# Mamba-1 steps and checkpoint writes: vector instructions per launch", "",
+             "Command (repository root as $R, an output directory as $OUT, run from /tmp with TMPDIR=/tmp):", "",
+             f"    {PROFILE_COMMANDS['entry_valu']}", f"    {PROFILE_COMMANDS['entry_valu_summary']}", "",
+             f"k_update_channels: {M1_LAYER[1]} channels x {M1_LAYER[0]} sequences x 16 entries, Weyl. k_update_rows: "
+             "checkpoint writes of a quarter of a hybrid layer (67,108,864 entries). Format codes: 0 fp16, 2 E4M3, 4 "
+             f"INT8. VALU busy = SQ_ACTIVE_INST_VALU x 4 / {simds} SIMDs / (GRBM_GUI_ACTIVE / {xcc} XCDs). Medians over the dispatches.", "",
+             "| kernel | waves | VALU instr per wave | per entry | VALU busy | LDS instr per wave | dispatches |",
+             "|---|---|---|---|---|---|---|"]
+    for k, c in sorted(vals.items()):
+        m = {n: statistics.median(v) for n, v in c.items()}
+        entries = M1_LAYER[0] * M1_LAYER[1] * 16 if "channels" in k else 64 * 128 * 64 * 128
+        busy = m["SQ_ACTIVE_INST_VALU"] * 4 / simds / (m["GRBM_GUI_ACTIVE"] / xcc)
+        lines.append(f"| `{_short_kernel(k)}` | {m['SQ_WAVES']:.0f} | {m['SQ_INSTS_VALU'] / m['SQ_WAVES']:.0f} | "
+                     f"{m['SQ_INSTS_VALU'] * 64 / entries:.1f} | {100 * busy:.0f} % | "
+                     f"{m['SQ_INSTS_LDS'] / m['SQ_WAVES']:.0f} | {len(c['SQ_WAVES'])} |")
+    os.makedirs(PROFILE_DIR, exist_ok=True)
+    with open(os.path.join(PROFILE_DIR, "k_update_channels.m1_b225.valu.md"), "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
     return 0
@@ -1216,15 +1259,23 @@ PROFILE_COMMANDS = {
     "entry_trace": "rocprofv3 --kernel-trace --stats --output-format csv -d $OUT/prof_entry "
                    "-o run -- python3 $R/bench.py --entry-points",
     "entry_trace_summary": "python3 $R/bench.py --summarize-entry-trace $OUT/prof_entry",
+    "entry_valu": "timeout -s KILL 120 rocprofv3 --pmc SQ_WAVES SQ_ACTIVE_INST_VALU SQ_INSTS_VALU "
+                  "SQ_INSTS_LDS GRBM_GUI_ACTIVE --output-format csv -d $OUT/pmc_entry -o run -- "
+                  "python3 $R/bench.py --entry-points --steps 20 --warmup 5",
+    "entry_valu_summary": "python3 $R/bench.py --summarize-entry-valu $OUT/pmc_entry",
     "replay_trace_summary": "python3 $R/bench.py --summarize-trace $OUT/prof_replay "
                             "k_replay.m1_long",
 }
 
 
+M1_LAYER = (225, 5120)  # sequences and channels of the large Mamba-1 batch
+
+
 def entry_point_rates(w, steps, warmup, device):
     """Rates of the boundary's other two calls on one layer's worth of entries: the
     rounding step alone (fp32 values in, codes and group scales out) and the
-    threshold words alone (32-bit words out). Each is timed over `steps` launches
+    threshold words alone (32-bit words out); and the times of checkpoint writes on a
+    quarter of the layer's batch and of steps of a large Mamba-1 batch. Each is timed over `steps` launches
     between two events on the launch stream; bytes are the call's own reads and
     writes (fp32 in 4 B, codes, 4 B per scale, 4 B per threshold word)."""
     import torch
@@ -1270,6 +1321,28 @@ def entry_point_rates(w, steps, warmup, device):
         us = timed(lambda k: ssmq.dither_fill(words, rule=rule, step=k, dither_block=w.dither_block,
                                               stream=stream))
         out["dither_fill"][rule] = {"us": us, "GBps": 4 * n / (us * 1e3), "bytes": 4 * n}
+    del h, words
+
+    def steps_of(family, b, heads, headdim, dstate, ngroups, fmt, group, **more):
+        A, D = wl.layer_params(family, heads, dstate, 1, device=device)
+        x, dt, B, C = wl.step_inputs(b, heads, headdim, dstate, ngroups, 2, device=device)
+        y = torch.empty((b, heads, headdim), device=device)
+        if more:
+            state = torch.randn((b, heads, headdim, dstate), generator=g, device=device) * 0.1
+            scale = torch.zeros(state.numel() // group, device=device) if group else None
+        else:
+            state, scale = wl.initial_state(fmt, b, heads, headdim, dstate, 3, group=group, device=device)
+        return timed(lambda k: ssmq.state_update(state, scale, x, dt, A, B, C, D, y, rule="weyl", fmt=fmt,
+                                                 dither_block=16, scale_group=group, step=k, stream=stream, **more))
+
+    b = w.batch // 4
+    out["checkpoint"] = {"entries": b * w.nheads * head}
+    for fmt, group in (("int8", 128), ("e4m3", 128), ("bf16", 0)):
+        out["checkpoint"][fmt] = steps_of("mamba2", b, w.nheads, w.headdim, w.dstate, w.ngroups, fmt, group,
+                                          fp32_state=True)
+    out["mamba1_step"] = {"batch": M1_LAYER[0], "channels": M1_LAYER[1]}
+    for fmt, group in (("int8", 16), ("e4m3", 16), ("fp16", 0)):
+        out["mamba1_step"][fmt] = steps_of("mamba1", *M1_LAYER, 1, 16, 1, fmt, group)
     return out
 
 
